@@ -561,6 +561,7 @@ int finger_search(const finger_tables* th, const float* queries, int64_t nq,
   L.vis_cap = pl.vis_cap;
   L.vis_probe = p->visited_probe ? p->visited_probe : 24;
   L.waves = pl.waves;
+  L.cus = cu_count();
   L.persistent = p->persistent;
   L.prefetch = p->code_prefetch > 0;
   L.coalesced = p->screen_layout != 2;

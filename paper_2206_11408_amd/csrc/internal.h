@@ -180,6 +180,7 @@ struct SearchLaunch {
   int vis_cap;
   int vis_probe;    // LDS slots a visited test examines before the spill table
   int waves;        // grid size in waves
+  int cus;          // CUs of the device
   int persistent;
   int prefetch;     // issue every slot's edge code with the adjacency row
   int coalesced;    // FINGER mode: coalesced screen (code rows of 32..256 bytes, degree <= 32)

@@ -49,6 +49,7 @@
 
 #include "device_common.h"
 #include "internal.h"
+#include "search_rule.h"
 
 namespace finger {
 
@@ -126,6 +127,7 @@ struct KArgs {
   uint32_t vis_mul, vis_id_mask;
   int vis_tag_bits;
   int waves_per_block;
+  int cus;  // (host) CUs of the device
   int coalesced;  // FINGER mode: use the coalesced screen where it applies
   int lds_wave_bytes;
   int lds_shared_bytes;
@@ -585,26 +587,12 @@ constexpr int vectors_in_flight() {
 }
 // Groups in a wide pass (0: none).  A vector longer than 128 takes one or
 // two dependent trips to memory per pass, and an expansion leaves several
-// times as many vectors as the narrow pass holds: the wide one keeps up to 32
-// float4 a lane in flight, and the registers cost less in waves than the
-// trips did, at every size of call (10,000 queries: 960 dimensions fp8
-// 1,730 us narrow, 1,470 wide; bf16 1,361 / 1,206; plain 3,287 / 3,189; 256
-// dimensions bf16 573 / 499; 33 queries x 960 297 / 248).  For 260 to 512
-// dimensions, and in plain search for 132 to 256, the narrow passes leave
-// twice the waves and that is worth more once they exist (480 dimensions,
-// 10,000 queries: bf16 619 us narrow, 737 wide; 4,096 queries: 338 / 316;
-// 1,024: 177 / 159; plain 132 to 256, 4,096 queries: 353 / 362; 1,024:
-// 192 / 172), so there the wide passes are for calls of up to kFewQueries
-// (FEW).
-constexpr int kFewQueries = 4096;
-template <int MODE, int G, int T4>
-constexpr bool wide_when_few() {
-  return G == 32 && (T4 == 4 || MODE == FINGER_MODE_PLAIN);
-}
-template <int MODE, int G, int T4, bool FEW>
+// times as many vectors as the narrow pass holds; the wide one keeps up to 32
+// float4 a lane in flight.  Which of them a launch takes: wide_passes.
+template <int MODE, int G, int T4, bool WIDE>
 constexpr int vectors_in_flight_wide() {
   if (G == 8 || (MODE != FINGER_MODE_PLAIN && MODE != FINGER_MODE_FINGER)) return 0;
-  if (wide_when_few<MODE, G, T4>() && !FEW) return MODE == FINGER_MODE_PLAIN ? 0 : 2;
+  if (!WIDE) return MODE == FINGER_MODE_FINGER && G == 32 && T4 == 4 ? 2 : 0;
   return T4 == 8 ? 4 : 8;
 }
 
@@ -701,7 +689,7 @@ __device__ __forceinline__ ColdArgs cold() {
 }
 
 // KArgs is the kernels' first argument (cold() reads it in place)
-template <int MODE, int CODE, int G, int T4, bool PREFETCH, int LC, bool FEW = false>
+template <int MODE, int CODE, int G, int T4, bool PREFETCH, int LC, bool WIDE>
 __device__ __forceinline__ void search_body(const KArgs& a) {
   // LC > 0: the coalesced screen (FINGER mode only); the query then stays in
   // registers when a lane needs at most four float4 of it and holds at most
@@ -1236,7 +1224,7 @@ __device__ __forceinline__ void search_body(const KArgs& a) {
       if (S2 == 0) continue;
       // 5. exact distances of the survivors
       const float dmine = exact_dists<G, T4, vectors_in_flight<MODE, G, T4>(),
-                                      vectors_in_flight_wide<MODE, G, T4, FEW>()>(a, qv, qlds, cid, S2);
+                                      vectors_in_flight_wide<MODE, G, T4, WIDE>()>(a, qv, qlds, cid, S2);
 
       // 6. admission: lanes 0..S2-1 hold (dmine, cid)
       uint64_t key = ~0ull;
@@ -1386,24 +1374,24 @@ __device__ __forceinline__ void search_body(const KArgs& a) {
   }
 }
 
-template <int MODE, int CODE, int G, int T4, bool PF, int LC>
+template <int MODE, int CODE, int G, int T4, bool PF, int LC, bool WIDE>
 __global__ void __launch_bounds__(256) k_search(KArgs a) {
-  search_body<MODE, CODE, G, T4, PF, LC>(a);
+  search_body<MODE, CODE, G, T4, PF, LC, WIDE>(a);
 }
 
-// a call of few queries (wide_when_few)
+// wide passes for calls whose queries are all resident at once
 template <int MODE, int CODE, int G, int T4, int LC>
 __global__ void __launch_bounds__(64) k_search_few(KArgs a) {
   search_body<MODE, CODE, G, T4, false, LC, true>(a);
 }
 
-// FINGER screening of short vectors and of many queries up to m = 512: hold
-// the register budget of four waves per SIMD (the search is latency bound,
-// so resident waves matter more than a few spills)
+// FINGER screening with narrow passes up to m = 512: hold the register budget
+// of four waves per SIMD (the search is latency bound, so resident waves
+// matter more than a few spills)
 template <int MODE, int CODE, int G, int T4, bool PF, int LC>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_search_w4(KArgs a) {
-  search_body<MODE, CODE, G, T4, PF, LC>(a);
+  search_body<MODE, CODE, G, T4, PF, LC, false>(a);
 }
 
 template <typename F>
@@ -1417,16 +1405,24 @@ hipError_t launch_fn(F fn, const KArgs& a, int blocks, int lds, hipStream_t s) {
 
 template <int MODE, int CODE, int G, int T4, bool PF, int LC>
 hipError_t launch_k(const KArgs& a, int blocks, int lds, hipStream_t s) {
-  if constexpr (!PF && wide_when_few<MODE, G, T4>() && (MODE == FINGER_MODE_PLAIN || (MODE == FINGER_MODE_FINGER && LC > 0)))
-    if (a.nq <= kFewQueries) return launch_fn(k_search_few<MODE, CODE, G, T4, LC>, a, blocks, lds, s);
-  // the register cap is for the shapes with narrow passes: the wide ones
+  constexpr bool kPlain = MODE == FINGER_MODE_PLAIN, kFinger = MODE == FINGER_MODE_FINGER;
+  // shapes with a wide instance: in FINGER mode of 260 to 512 dimensions only
+  // the coalesced screen's that requests codes after the visited test
+  constexpr bool kFew = (kPlain && G == 32) || (kFinger && G == 32 && T4 == 4 && LC > 0 && !PF);
+  constexpr bool kWide = kFew || ((kPlain || kFinger) && (G == 64 || (G == 32 && T4 == 2)));
+  if constexpr (kWide)
+    if (wide_passes(kPlain, G, T4, a.nq, blocks * a.waves_per_block, a.cus)) {
+      if constexpr (kFew) return launch_fn(k_search_few<MODE, CODE, G, T4, LC>, a, blocks, lds, s);
+      else return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, true>, a, blocks, lds, s);
+    }
+  // the register cap is for narrow passes of up to 512 dimensions: wide ones
   // would spill (256 dimensions, bf16, 1,024 queries: 158 us capped, 149
   // not), and at 8 float4 per lane a capped build also returned run-to-run
   // differing results with BF16 codes requested ahead
-  if constexpr (MODE == FINGER_MODE_FINGER && (G == 8 || wide_when_few<MODE, G, T4>()))
+  if constexpr (kFinger && G < 64)
     return launch_fn(k_search_w4<MODE, CODE, G, T4, PF, LC>, a, blocks, lds, s);
   else
-    return launch_fn(k_search<MODE, CODE, G, T4, PF, LC>, a, blocks, lds, s);
+    return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, false>, a, blocks, lds, s);
 }
 
 // Lanes per vector and float4 per lane: as few float4 as cover m (a lane's

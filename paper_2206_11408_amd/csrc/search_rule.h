@@ -1,0 +1,36 @@
+// Which instance a search launch takes (host arithmetic only; the instances
+// are in search_kernel.h).
+#pragma once
+
+#include <cstdint>
+
+namespace finger {
+
+// Query waves per CU that the registers of a wide-pass instance leave (two
+// waves per SIMD; three for 132 to 256 dimensions, four in plain search).
+constexpr int wide_waves_per_cu(bool plain, int g, int t4) {
+  return g == 32 && t4 == 2 ? (plain ? 16 : 12) : 8;
+}
+
+// Wide or narrow passes of exact distances for vectors longer than 128 (g
+// lanes to a vector, t4 float4 a lane).  nq queries on `waves` query waves.
+//
+// A wide pass makes fewer dependent trips to memory and leaves fewer resident
+// waves.  While every query has a wave at once anyway, the trips are what
+// counts: 1,000 queries, ef 16 / 100, wide against narrow: 256 dimensions bf16
+// 1.48 / 1.22 times as fast, 512 bf16 1.23 / 1.11, 960 fp8 1.25 / 1.17, 2,048
+// plain 1.02 / 1.06.  Past that a second, mostly empty round of waves costs
+// more than the trips save (narrow against wide at 2,500 queries: 300 f32
+// 1.32 / 1.46, 480 bf16 1.17 / 1.38, 960 bf16 1.21 / 1.31, 1,028 bf16 1.29 /
+// 1.35; at 3,500: 192 bf16 1.17 / 1.28).  From about 9,000 queries on there
+// are rounds enough for the partial one not to matter, and the wide passes
+// of 132 to 256 dimensions in FINGER mode and of 516 to 1,024 win again
+// (10,000 queries: 256 bf16 1.23 / 1.02, 960 fp8 1.17 / 0.98, 960 plain 0.97 /
+// 1.07); the other shapes' do not.
+constexpr bool wide_passes(bool plain, int g, int t4, int64_t nq, int64_t waves, int cus) {
+  if (g == 8) return false;
+  if (nq <= (int64_t)wide_waves_per_cu(plain, g, t4) * cus || waves <= (int64_t)8 * cus) return true;
+  return (g == 64 ? t4 == 4 : t4 == 2 && !plain) && nq >= (int64_t)36 * cus;
+}
+
+}  // namespace finger

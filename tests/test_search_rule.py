@@ -1,0 +1,66 @@
+"""The launch rules of the search (host arithmetic, compiled by itself)."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CUS = 256
+PROGRAM = r"""
+#include <cstdio>
+#include "search_rule.h"
+int main() {
+  char what;
+  long long a, b, c, d, e, f;
+  while (scanf(" %c %lld %lld %lld %lld %lld %lld", &what, &a, &b, &c, &d, &e, &f) == 7)
+    printf("%d\n", what == 'w' && finger::wide_passes(a, b, c, d, e, f));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rule")
+    (d / "rule.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2206_11408_amd", "csrc"),
+                    str(d / "rule.cpp"), "-o", str(d / "rule")], check=True)
+
+    def run(rows):
+        text = "".join(" ".join(map(str, r + (0,) * (7 - len(r)))) + "\n" for r in rows)
+        out = subprocess.run([str(d / "rule")], input=text, capture_output=True, text=True, check=True).stdout
+        return [int(x) for x in out.split()]
+    return run
+
+
+# (plain, lanes per vector, float4 per lane): waves per CU of the wide instance
+SHAPES = {(0, 32, 2): 12, (1, 32, 2): 16, (0, 32, 4): 8, (1, 32, 4): 8, (0, 64, 4): 8, (1, 64, 4): 8, (0, 64, 8): 8,
+          (1, 64, 8): 8}
+
+
+def wide(ask, shape, nqs, per_cu=16):
+    return ask([("w", *shape, nq, min(nq, per_cu * CUS), CUS) for nq in nqs])
+
+
+@pytest.mark.parametrize("shape,waves", SHAPES.items())
+def test_wide_while_every_query_is_resident(ask, shape, waves):
+    fit = waves * CUS
+    assert wide(ask, shape, [1, 33, fit - 1, fit]) == [1, 1, 1, 1]
+    # one more query is a second round of waves
+    assert wide(ask, shape, [fit + 1, fit + fit // 4, 2 * fit - 1 if waves < 16 else fit + 1]) == [0, 0, 0]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_wide_again_for_many_queries(ask, shape):
+    again = shape in ((0, 32, 2), (0, 64, 4), (1, 64, 4))
+    assert wide(ask, shape, [36 * CUS - 1, 36 * CUS, 100_000]) == [0, again, again]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_wide_where_registers_do_not_bind(ask, shape):
+    """LDS or the caller holds the launch to eight waves a CU or fewer."""
+    assert wide(ask, shape, [1000, 5000, 50_000], per_cu=8) == [1, 1, 1]
+
+
+def test_never_wide_for_short_vectors(ask):
+    assert ask([("w", p, 8, t, nq, min(nq, 4096), CUS) for p in (0, 1) for t in (1, 2, 3, 4)
+                for nq in (1, 5000, 100_000)]) == [0] * 24
