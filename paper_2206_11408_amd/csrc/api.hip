@@ -562,6 +562,7 @@ int finger_search(const finger_tables* th, const float* queries, int64_t nq,
   L.vis_probe = p->visited_probe ? p->visited_probe : 24;
   L.waves = pl.waves;
   L.cus = cu_count();
+  L.fit_grid = p->waves_per_cu == 0;
   L.persistent = p->persistent;
   L.prefetch = p->code_prefetch > 0;
   L.coalesced = p->screen_layout != 2;

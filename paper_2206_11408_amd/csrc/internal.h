@@ -181,6 +181,7 @@ struct SearchLaunch {
   int vis_probe;    // LDS slots a visited test examines before the spill table
   int waves;        // grid size in waves
   int cus;          // CUs of the device
+  bool fit_grid;    // a static grid may shrink to what is resident
   int persistent;
   int prefetch;     // issue every slot's edge code with the adjacency row
   int coalesced;    // FINGER mode: coalesced screen (code rows of 32..256 bytes, degree <= 32)

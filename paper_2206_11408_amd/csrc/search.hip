@@ -108,6 +108,7 @@ hipError_t launch_search(const Tables& t, const SearchLaunch& L, hipStream_t s) 
   // one query wave per workgroup keeps LDS allocation fine grained
   a.waves_per_block = 1;
   a.cus = L.cus;
+  a.fit_grid = L.fit_grid;
   a.coalesced = L.coalesced;
   a.lds_shared_bytes = 0;
   a.lds_wave_bytes = wave_bytes(L.ef_max, L.vis_cap, L.mode == FINGER_MODE_PLAIN ? 0 : t.r, t.m,

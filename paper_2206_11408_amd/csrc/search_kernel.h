@@ -127,7 +127,7 @@ struct KArgs {
   uint32_t vis_mul, vis_id_mask;
   int vis_tag_bits;
   int waves_per_block;
-  int cus;  // (host) CUs of the device
+  int cus, fit_grid;  // (host) CUs; the grid may shrink to what is resident
   int coalesced;  // FINGER mode: use the coalesced screen where it applies
   int lds_wave_bytes;
   int lds_shared_bytes;
@@ -488,7 +488,7 @@ __device__ __forceinline__ void dists_pass(const KArgs& a, const float4* qv, con
       for (int t = 0; t < T4; ++t) xv[h][t] = x4[G * t];
     }
     // (the scheduler would sink the loads of a wide pass to their use, two at
-    // a time, each a dependent trip: 500 queries x 2,048 plain 0.8 times the
+    // a time, each a dependent trip: 500 queries x 2,048 plain 0.67 times the
     // speed of narrow passes, 1.0 with the loads held together)
     if constexpr (NP * T4 > 16) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1403,6 +1403,13 @@ hipError_t launch_fn(F fn, const KArgs& a, int blocks, int lds, hipStream_t s) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
+  if (a.fit_grid && !a.persistent && blocks < a.nq) {
+    int per_cu = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn),
+                                                     64 * a.waves_per_block, lds);
+    if (e != hipSuccess) return e;
+    blocks = resident_blocks(blocks, a.nq, per_cu, a.cus);
+  }
   hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * a.waves_per_block), lds, s, a);
   return hipGetLastError();
 }

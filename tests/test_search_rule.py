@@ -13,7 +13,7 @@ int main() {
   char what;
   long long a, b, c, d, e, f;
   while (scanf(" %c %lld %lld %lld %lld %lld %lld", &what, &a, &b, &c, &d, &e, &f) == 7)
-    printf("%d\n", what == 'w' && finger::wide_passes(a, b, c, d, e, f));
+    printf("%d\n", what == 'w' ? (int)finger::wide_passes(a, b, c, d, e, f) : finger::resident_blocks(a, b, c, d));
 }
 """
 
@@ -64,3 +64,11 @@ def test_wide_where_registers_do_not_bind(ask, shape):
 def test_never_wide_for_short_vectors(ask):
     assert ask([("w", p, 8, t, nq, min(nq, 4096), CUS) for p in (0, 1) for t in (1, 2, 3, 4)
                 for nq in (1, 5000, 100_000)]) == [0] * 24
+
+
+def test_static_grid_is_what_is_resident(ask):
+    # several queries to a workgroup: no partial round of workgroups
+    assert ask([("r", 4096, 20_000, 12, CUS), ("r", 3584, 20_000, 8, CUS), ("r", 4096, 4097, 8, CUS)]) == [3072, 2048, 2048]
+    # a workgroup per query, or all of them resident
+    assert ask([("r", 4096, 4096, 8, CUS), ("r", 1000, 1000, 2, CUS), ("r", 3072, 20_000, 16, CUS),
+                ("r", 3072, 20_000, 0, CUS)]) == [4096, 1000, 3072, 3072]
