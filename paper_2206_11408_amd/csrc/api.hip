@@ -880,15 +880,18 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
   if (roots > 0) {
     HIPCHK(launch_root_list(n, stamp.p, kb.p, fa.p, s));
     constexpr int J = 16;  // nearest reached nodes listed per start node
-    const int j = (int)std::min<int64_t>(J, n), per = W + 1 + 2 * j;
+    const int j = (int)std::min<int64_t>(J, n), per = W + 4 + 3 * j;
     const int64_t rb = std::min<int64_t>(roots, 65536);
-    DevBuf<float> rq, rd;
+    DevBuf<float> rq, rd, rdist;
+    DevBuf<float2> rb_bound;
     DevBuf<int32_t> rid, rinfo;
     DevBuf<char> rws;
     const size_t rws_bytes = exact_knn_ws_bytes(n, m, rb, j);
     alloc(rq, (size_t)rb * m * 4, "start nodes");
     alloc(rd, (size_t)rb * j * 4, "nearest distances");
     alloc(rid, (size_t)rb * j * 4, "nearest ids");
+    alloc(rdist, (size_t)rb * j * 4, "nearest distances");
+    alloc(rb_bound, (size_t)rb * 8, "nearest bounds");
     alloc(rinfo, (size_t)rb * per * 4, "repair rows");
     alloc(rws, rws_bytes, "kNN workspace");
     if (rc != FINGER_OK) return rc;
@@ -917,25 +920,36 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
         const int64_t nr = std::min(rb, roots - r0);
         const KnnFilter filter{free_label.p, fa.p + r0};
         HIPCHK(launch_gather_rows(X, m, fa.p + r0, nr, rq.p, s));
-        HIPCHK(launch_exact_knn(X, n, m, rq.p, nr, j, FINGER_L2, rid.p, rd.p, rws.p, rws_bytes, s, &filter));
-        HIPCHK(launch_repair_gather(out_graph, W, deg.p, fa.p + r0, nr, rid.p, j, rinfo.p, s));
+        HIPCHK(launch_exact_knn(X, n, m, rq.p, nr, j, FINGER_L2, rid.p, rd.p, rws.p, rws_bytes, s, &filter,
+                                rb_bound.p));
+        HIPCHK(launch_repair_gather(X, m, out_graph, W, deg.p, fa.p + r0, nr, rid.p, rd.p, rb_bound.p, j, rdist.p,
+                                    rinfo.p, s));
         HIPCHK(hipMemcpyAsync(info.data(), rinfo.p, (size_t)nr * per * 4, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         for (int64_t r = 0; r < nr; ++r) {
           const int32_t u = root_h[(size_t)(r0 + r)];
           const int32_t* row = info.data() + r * per;
           const int32_t* cand = row + W + 1;
+          auto dist = [&](int c) {
+            float f;
+            std::memcpy(&f, cand + 2 * j + c, 4);
+            return f;
+          };
+          // the nearest listed node that still has a free slot, if every
+          // node not listed is certainly further away
           int32_t v = -1, dv = 0;
+          float best_d = 0.f;
           for (int c = 0; c < j && cand[c] >= 0; ++c) {
             const int32_t d = degree(cand[c], cand[j + c]);
-            if (d < W) {
+            if (d < W && (v < 0 || dist(c) < best_d || (dist(c) == best_d && cand[c] < v))) {
               v = cand[c];
               dv = d;
-              break;
+              best_d = dist(c);
             }
           }
+          if (v >= 0 && !knn_certain(best_d, dist(j), dist(j + 1), dist(j + 2), m)) v = -1;
           if (v < 0) {
-            // every listed node has filled up since: search them all
+            // the short list does not settle it: search all nodes
             if (best.p == nullptr) {
               alloc(best, 8, "nearest key");
               if (rc != FINGER_OK) return rc;

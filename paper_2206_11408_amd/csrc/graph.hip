@@ -13,9 +13,11 @@
 // comes from propagating minima along the edges; the nearest reached nodes
 // of all start nodes then come from one kNN call restricted to smaller
 // labels, and the host only walks the short lists to keep track of the free
-// slots.  Step by step on the host (a search of the whole set and a
-// breadth-first walk each, several round trips) took 42 ms for the 100
-// components of a 100,000 x 128 mixture; this takes
+// slots.  Where a list does not settle which node is nearest (candidate
+// scores or distances too close for their rounding, or no free slot left in
+// it) all nodes are searched for that step.  Step by step on the host (a
+// search of the whole set and a breadth-first walk each, several round trips)
+// took 42 ms for the 100 components of a 100,000 x 128 mixture; this takes
 // 1.2 ms.
 //
 // Edge e of the 2nk directed edges: e < nk is the kNN edge (e / k -> ids[e])
@@ -122,6 +124,7 @@ __device__ __forceinline__ void load_vec(const float4* data, int m4, int id, int
   }
 }
 
+// (fused multiply-adds written out: the same bits in every kernel)
 template <int G, int T4>
 __device__ __forceinline__ float sq_dist(const float4 (&a)[T4], const float4 (&b)[T4]) {
   float acc = 0.f;
@@ -129,7 +132,8 @@ __device__ __forceinline__ float sq_dist(const float4 (&a)[T4], const float4 (&b
   for (int t = 0; t < T4; ++t) {
     const float dx = a[t].x - b[t].x, dy = a[t].y - b[t].y;
     const float dz = a[t].z - b[t].z, dw = a[t].w - b[t].w;
-    acc += dx * dx + dy * dy + dz * dz + dw * dw;
+    const float s = __builtin_fmaf(dw, dw, __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)));
+    acc = t == 0 ? s : acc + s;
   }
   return group_sum<G>(acc);
 }
@@ -228,23 +232,49 @@ __global__ void k_root_list(int64_t n, const uint32_t* flag, const uint32_t* pos
   if (i < n && flag[i] != 0u) roots[pos[i]] = (int32_t)i;
 }
 
-// per start node: its row, its degree, the candidates and their degrees
+// dist[r][c]: the distance of candidate c to start node r as k_nearest_free
+// has it (one wave per start node; infinity where the list has ended)
+template <int G, int T4>
+__global__ __launch_bounds__(256) void k_repair_dists(const float4* data, int m4, const int32_t* roots, int64_t cnt,
+                                                      const int32_t* cand, int J, float* dist) {
+  constexpr int NPAR = 64 / G;
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= cnt) return;
+  const int lg = lane % G, grp = lane / G;
+  float4 xu[T4];
+  load_vec<G, T4>(data, m4, roots[r], lg, true, xu);
+  for (int c0 = 0; c0 < J; c0 += NPAR) {
+    const int c = c0 + grp;
+    const int id = c < J ? cand[r * J + c] : -1;
+    float4 xv[T4];
+    load_vec<G, T4>(data, m4, id, lg, id >= 0, xv);
+    const float d = sq_dist<G, T4>(xu, xv);
+    if (c < J && lg == 0) dist[r * J + c] = id >= 0 ? d : __int_as_float(0x7f800000);
+  }
+}
+
+// per start node: its row, its degree, the candidates, their degrees and
+// distances, the kNN's last distance, its score bound and |q|^2 (floats as
+// bits)
 __global__ void k_repair_gather(const int32_t* G, int W, const int32_t* deg, const int32_t* roots, int64_t cnt,
-                                const int32_t* cand, int J, int32_t* out) {
-  const int per = W + 1 + 2 * J;
+                                const int32_t* cand, const float* dist, const float* knn_dist, const float2* bound,
+                                int J, int32_t* out) {
+  const int per = W + 4 + 3 * J;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= cnt * per) return;
   const int64_t r = i / per;
-  const int c = (int)(i % per);
+  int c = (int)(i % per);
   const int32_t u = roots[r];
   int32_t v;
   if (c < W) v = G[(int64_t)u * W + c];
   else if (c == W) v = deg[u];
-  else if (c <= W + J) v = cand[r * J + c - W - 1];
-  else {
-    const int32_t id = cand[r * J + c - W - 1 - J];
+  else if ((c -= W + 1) < J) v = cand[r * J + c];
+  else if ((c -= J) < J) {
+    const int32_t id = cand[r * J + c];
     v = id >= 0 ? deg[id] : 0;
-  }
+  } else if ((c -= J) < J) v = __float_as_int(dist[r * J + c]);
+  else v = __float_as_int(c == J ? knn_dist[r * J + J - 1] : c == J + 1 ? bound[r].x : bound[r].y);
   out[i] = v;
 }
 
@@ -254,7 +284,8 @@ __global__ void k_scatter_i32(const int64_t* at, const int32_t* val, int64_t cnt
 }
 
 // smallest (squared distance to u, id) over the nodes with a smaller label
-// and a free slot (when a start node's short list holds none any more)
+// and a free slot (when a start node's short list holds none any more, or
+// does not settle which is nearest)
 template <int G, int T4>
 __global__ __launch_bounds__(256) void k_nearest_free(const float4* data, int64_t n, int m4, int u,
                                                       const uint32_t* label, const int32_t* deg,
@@ -288,6 +319,16 @@ __global__ __launch_bounds__(256) void k_nearest_free(const float4* data, int64_
     if (b != ~0ull) atomicMin(best, (unsigned long long)b);
   }
 }
+
+// lanes per vector and float4 per lane by vector length (the shape fixes the
+// order of a distance's sum)
+#define FINGER_BY_LENGTH(m4, LAUNCH)  \
+  if (m4 <= 16) LAUNCH(16, 1);        \
+  else if (m4 <= 32) LAUNCH(16, 2);   \
+  else if (m4 <= 64) LAUNCH(16, 4);   \
+  else if (m4 <= 128) LAUNCH(16, 8);  \
+  else if (m4 <= 256) LAUNCH(64, 4);  \
+  else LAUNCH(64, 8);
 
 inline unsigned blocks_for(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
 
@@ -353,12 +394,7 @@ hipError_t launch_prune(const float* data, int64_t n, int m, const uint32_t* ind
   const int m4 = m / 4;
   const dim3 grid(blocks_for(n, 4)), block(256);
 #define FINGER_PRUNE(G_, T_) hipLaunchKernelGGL((k_prune<G_, T_>), grid, block, 0, s, d4, n, m4, indptr, nbr, nd, W, out)
-  if (m4 <= 16) FINGER_PRUNE(16, 1);
-  else if (m4 <= 32) FINGER_PRUNE(16, 2);
-  else if (m4 <= 64) FINGER_PRUNE(16, 4);
-  else if (m4 <= 128) FINGER_PRUNE(16, 8);
-  else if (m4 <= 256) FINGER_PRUNE(64, 4);
-  else FINGER_PRUNE(64, 8);
+  FINGER_BY_LENGTH(m4, FINGER_PRUNE)
 #undef FINGER_PRUNE
   return hipGetLastError();
 }
@@ -392,11 +428,18 @@ hipError_t launch_root_list(int64_t n, const uint32_t* flag, const uint32_t* pos
   return hipGetLastError();
 }
 
-hipError_t launch_repair_gather(const int32_t* G, int W, const int32_t* deg, const int32_t* roots, int64_t cnt,
-                                const int32_t* cand, int J, int32_t* out, hipStream_t s) {
+hipError_t launch_repair_gather(const float* data, int m, const int32_t* G, int W, const int32_t* deg,
+                                const int32_t* roots, int64_t cnt, const int32_t* cand, const float* knn_dist,
+                                const float2* bound, int J, float* dist, int32_t* out, hipStream_t s) {
   if (cnt == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_repair_gather, dim3(blocks_for(cnt * (W + 1 + 2 * J))), dim3(256), 0, s, G, W, deg, roots, cnt,
-                     cand, J, out);
+  const float4* d4 = reinterpret_cast<const float4*>(data);
+  const int m4 = m / 4;
+  const dim3 grid(blocks_for(cnt, 4)), block(256);
+#define FINGER_RDIST(G_, T_) hipLaunchKernelGGL((k_repair_dists<G_, T_>), grid, block, 0, s, d4, m4, roots, cnt, cand, J, dist)
+  FINGER_BY_LENGTH(m4, FINGER_RDIST)
+#undef FINGER_RDIST
+  hipLaunchKernelGGL(k_repair_gather, dim3(blocks_for(cnt * (W + 4 + 3 * J))), dim3(256), 0, s, G, W, deg, roots, cnt,
+                     cand, dist, knn_dist, bound, J, out);
   return hipGetLastError();
 }
 
@@ -412,12 +455,7 @@ hipError_t launch_nearest_free(const float* data, int64_t n, int m, int u, const
   const int m4 = m / 4;
   const dim3 grid((unsigned)std::min<int64_t>(4096, (n + 15) / 16)), block(256);
 #define FINGER_NEAR(G_, T_) hipLaunchKernelGGL((k_nearest_free<G_, T_>), grid, block, 0, s, d4, n, m4, u, label, deg, W, best)
-  if (m4 <= 16) FINGER_NEAR(16, 1);
-  else if (m4 <= 32) FINGER_NEAR(16, 2);
-  else if (m4 <= 64) FINGER_NEAR(16, 4);
-  else if (m4 <= 128) FINGER_NEAR(16, 8);
-  else if (m4 <= 256) FINGER_NEAR(64, 4);
-  else FINGER_NEAR(64, 8);
+  FINGER_BY_LENGTH(m4, FINGER_NEAR)
 #undef FINGER_NEAR
   return hipGetLastError();
 }

@@ -139,8 +139,10 @@ hipError_t launch_label_sweep(const int32_t* G, int64_t n, int W, const int32_t*
 hipError_t launch_root_flags(int64_t n, const uint32_t* label, const int32_t* deg, int W, uint32_t* flag,
                              uint32_t* free_label, hipStream_t s);
 hipError_t launch_root_list(int64_t n, const uint32_t* flag, const uint32_t* pos, int32_t* roots, hipStream_t s);
-hipError_t launch_repair_gather(const int32_t* G, int W, const int32_t* deg, const int32_t* roots, int64_t cnt,
-                                const int32_t* cand, int J, int32_t* out, hipStream_t s);
+// per start node W + 4 + 3 J words (k_repair_gather); dist [cnt][J] is scratch
+hipError_t launch_repair_gather(const float* data, int m, const int32_t* G, int W, const int32_t* deg,
+                                const int32_t* roots, int64_t cnt, const int32_t* cand, const float* knn_dist,
+                                const float2* bound, int J, float* dist, int32_t* out, hipStream_t s);
 hipError_t launch_scatter_i32(const int64_t* at, const int32_t* val, int64_t cnt, int32_t* dst, hipStream_t s);
 hipError_t launch_nearest_free(const float* data, int64_t n, int m, int u, const uint32_t* label,
                                const int32_t* deg, int W, unsigned long long* best, hipStream_t s);
@@ -249,7 +251,15 @@ struct KnnFilter {
 };
 hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q, int64_t nq,
                             int k, int metric, int32_t* ids, float* dist, void* ws,
-                            size_t ws_bytes, hipStream_t s, const KnnFilter* filter = nullptr);
+                            size_t ws_bytes, hipStream_t s, const KnnFilter* filter = nullptr,
+                            float2* bound = nullptr);
+// bound[i] of the call above: (no candidate score of a point outside the
+// exact re-rank is smaller; infinity if none is outside, |q_i|^2)
+
+// whether distance d is certainly below those of all points that the call
+// above could have listed and did not: its list ends at `last`, the scores of
+// the points outside the re-rank begin at `score`
+bool knn_certain(float d, float last, float score, float qq, int m);
 
 // gate
 hipError_t launch_mlp_forward(const float* w, int in, int H, const float* x, int64_t B, float* y,

@@ -643,6 +643,9 @@ struct FinalArgs {
   KnnFilter f;
   int32_t* ids;
   float* dist;
+  const uint64_t* tauk;
+  const float* qn;
+  float2* bound;  // see launch_exact_knn (may be NULL)
 };
 
 __device__ __forceinline__ float knn_term(const FinalArgs& a, float q, float x, double qi, double xi, float d) {
@@ -664,6 +667,10 @@ __global__ void __launch_bounds__(256) k_knn_final(FinalArgs a) {
   const int64_t row = blockIdx.x, q = a.row0 + row;
   const float* qv = a.q + q * a.m;
   const double qi = a.qinv != nullptr ? a.qinv[q] : 1.0;
+  if (a.bound != nullptr && t == 0) {
+    const uint64_t tk = a.over[row] == 0 ? a.tauk[row] : ~0ull;
+    a.bound[q] = make_float2(tk == ~0ull ? __int_as_float(0x7f800000) : order_bits_inv((uint32_t)(tk >> 32)), a.qn[q]);
+  }
   int keep;
   if (a.over[row] == 0) {
     const uint64_t* best = a.best + row * a.KK;
@@ -824,8 +831,25 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s) {
 
 size_t exact_knn_ws_bytes(int64_t n, int m, int64_t nq, int k) { return knn_plan(n, m, nq, k).total; }
 
+bool knn_certain(float d, float last, float score, float qq, int m) {
+  // A float32 distance is a sum of squares with at most 64 roundings on any
+  // path (m <= 2048), so two of them order as the exact ones do when they
+  // differ by more than 2^-16 of themselves, whatever their order of sums.
+  constexpr double rel = 1.0 / 65536;
+  if (!(d < last * (1.0 - rel))) return false;
+  // Scores: with Q = |q| and X = |x| the products left out by the split are
+  // below 3 2^-18 Q X, and 3 m products, the norms' 2 m and the start value are
+  // added with an error of 2^-23 of the largest partial sum each.  Points with
+  // X > Q + sqrt(d) are further away than d in any case.
+  const double e = m / 8388608.0, Q = std::sqrt((double)qq) * (1.0 + e);
+  const double X = (Q + std::sqrt((double)d)) * (1.0 + rel);
+  const double err = Q * X * (1.0 / 32768 + 6.2 * e) + X * X * 4.0 * e + Q * Q * e + 1e-30;
+  return (double)d * (1.0 + rel) < (double)score - err && err < 1e37;
+}
+
 hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q, int64_t nq, int k, int metric,
-                            int32_t* ids, float* dist, void* ws, size_t ws_bytes, hipStream_t s, const KnnFilter* filter) {
+                            int32_t* ids, float* dist, void* ws, size_t ws_bytes, hipStream_t s, const KnnFilter* filter,
+                            float2* bound) {
   if (nq == 0) return hipSuccess;
   const KnnPlan p = knn_plan(n, m, nq, k);
   if (ws_bytes < p.total) return hipErrorInvalidValue;
@@ -967,6 +991,9 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
     f.f = c.f;
     f.ids = ids;
     f.dist = dist;
+    f.tauk = v.tauk;
+    f.qn = qn;
+    f.bound = bound;
     hipLaunchKernelGGL(k_knn_final, dim3((unsigned)rows), dim3(256), fin_lds, s, f);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
