@@ -11,10 +11,9 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
-#include <system_error>
-#include <thread>
 
 #include "../../include/finger.h"
+#include "host_slices.h"
 #include "internal.h"
 
 namespace finger {
@@ -93,43 +92,34 @@ inline int cu_count() {
 // dst (host, pageable) <- src on device `dev`, complete on return.  Large
 // tables go in slices, one host thread and stream each: one thread moves
 // 10 GB/s into fresh memory (its page faults and the staging copy are
-// serial), four move 34 GB/s.  Below 8 MB, or where a thread or stream cannot
-// be had, one plain copy does (the same bytes).
+// serial), four move 34 GB/s.  The first page goes by the plain copy, which
+// waits for what a plain copy of everything would wait for.  Below 8 MB, or
+// where a thread or stream cannot be had, one plain copy does (the same
+// bytes).
 inline hipError_t copy_to_host(void* dst, const void* src, size_t bytes, int dev) {
-  constexpr size_t kSlice = (size_t)4 << 20;
-  constexpr int kMaxThreads = 4;
-  const int slices = (int)std::min<size_t>(kMaxThreads, bytes / kSlice);
+  constexpr size_t kSlice = (size_t)4 << 20, kFirst = 4096;
+  constexpr int kThreads = 4;
+  static_assert(kThreads <= kMaxSlices, "one thread per slice");
+  const int slices = (int)std::min<size_t>(kThreads, bytes / kSlice);
   if (slices < 2) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
-  hipError_t e = hipStreamSynchronize(nullptr);  // as the plain copy waits for the null stream
+  const hipError_t e = hipMemcpy(dst, src, kFirst, hipMemcpyDeviceToHost);
   if (e != hipSuccess) return e;
   const size_t per = (bytes / slices + 4095) / 4096 * 4096;
-  hipError_t err[kMaxThreads];
+  hipError_t err[kThreads] = {};
   auto move = [&](int i) {
-    const size_t at = per * (size_t)i;
-    const size_t len = i + 1 == slices ? bytes - at : per;
+    const size_t at = i == 0 ? kFirst : per * (size_t)i;
+    const size_t end = i + 1 == slices ? bytes : per * (size_t)(i + 1);
     hipStream_t s = nullptr;
     err[i] = hipSetDevice(dev);
     if (err[i] == hipSuccess) err[i] = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
     if (err[i] != hipSuccess) return;
-    err[i] = hipMemcpyAsync(static_cast<char*>(dst) + at, static_cast<const char*>(src) + at, len,
+    err[i] = hipMemcpyAsync(static_cast<char*>(dst) + at, static_cast<const char*>(src) + at, end - at,
                             hipMemcpyDeviceToHost, s);
     const hipError_t w = hipStreamSynchronize(s);
     if (err[i] == hipSuccess) err[i] = w;
     (void)hipStreamDestroy(s);
   };
-  std::thread th[kMaxThreads];
-  bool all = true;
-  for (int i = 0; i < slices; ++i) {
-    err[i] = hipSuccess;
-    try {
-      th[i] = std::thread(move, i);
-    } catch (const std::system_error&) {
-      all = false;
-      break;
-    }
-  }
-  for (int i = 0; i < slices; ++i)
-    if (th[i].joinable()) th[i].join();
+  bool all = run_sliced(slices, move);
   for (int i = 0; i < slices; ++i) all = all && err[i] == hipSuccess;
   return all ? hipSuccess : hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
 }
