@@ -93,19 +93,17 @@ inline int cu_count() {
 // tables go in slices, one host thread and stream each: one thread moves
 // 10 GB/s into fresh memory (its page faults and the staging copy are
 // serial), four move 34 GB/s.  The first page goes by the plain copy, which
-// waits for what a plain copy of everything would wait for.  Below 8 MB, or
+// waits for what a plain copy of everything would wait for.  Smaller ones, or
 // where a thread or stream cannot be had, one plain copy does (the same
 // bytes).
 inline hipError_t copy_to_host(void* dst, const void* src, size_t bytes, int dev) {
-  constexpr size_t kSlice = (size_t)4 << 20, kFirst = 4096;
-  constexpr int kThreads = 4;
-  static_assert(kThreads <= kMaxSlices, "one thread per slice");
-  const int slices = (int)std::min<size_t>(kThreads, bytes / kSlice);
+  constexpr size_t kFirst = 4096;
+  const int slices = copy_slices(bytes);
   if (slices < 2) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
   const hipError_t e = hipMemcpy(dst, src, kFirst, hipMemcpyDeviceToHost);
   if (e != hipSuccess) return e;
   const size_t per = (bytes / slices + 4095) / 4096 * 4096;
-  hipError_t err[kThreads] = {};
+  hipError_t err[kMaxSlices] = {};
   auto move = [&](int i) {
     const size_t at = i == 0 ? kFirst : per * (size_t)i;
     const size_t end = i + 1 == slices ? bytes : per * (size_t)(i + 1);

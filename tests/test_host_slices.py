@@ -23,6 +23,7 @@ void* operator new(std::size_t n) {
 void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 int main(int, char** argv) {
+  if (argv[1][0] == 'n') return std::printf("%d\n", finger::copy_slices(std::strtoull(argv[2], nullptr, 10))), 0;
   std::atomic<int> ran{0}, sum{0};
   left = std::atoi(argv[1]);
   const bool all = finger::run_sliced(std::atoi(argv[2]), [&](int i) { ++ran; sum += i; });
@@ -52,3 +53,9 @@ def test_no_memory_for_a_thread(program, fail_at):
     assert r.returncode == 0, r.stderr
     all_ran, ran, _ = map(int, r.stdout.split())
     assert all_ran == 0 and ran < 4
+
+
+def test_slices_only_where_they_pay(program):
+    mb = 1 << 20
+    got = [int(program("n", b).stdout) for b in (0, 10 * mb, 41 * mb, 64 * mb - 1, 64 * mb, 1 << 33)]
+    assert got == [1, 1, 1, 1, 4, 4]
