@@ -1,9 +1,14 @@
-// Symmetric eigendecomposition in float64 by the cyclic Jacobi method with
-// the round-robin ("parallel") order of pivots (Golub and Van Loan, "Matrix
-// Computations", the parallel ordering of the cyclic Jacobi algorithm).  Used
-// once per build on the m x m second-moment matrix of the sampled residuals,
-// whose top-r eigenvectors are the left singular vectors Proposition 3.1 asks
-// for.
+// Symmetric eigendecomposition in float64 by the cyclic Jacobi method (Golub
+// and Van Loan, "Matrix Computations", the cyclic Jacobi algorithm and its
+// parallel ordering).  Used once per build on the m x m second-moment matrix of
+// the sampled residuals, whose top-r eigenvectors are the left singular vectors
+// Proposition 3.1 asks for.
+//
+// Up to kHostDim a host core does it, row by row: the matrix sits in its L1,
+// while the GPU pays a barrier per step and a round trip per sweep (a whole
+// build of 2,000 points: m = 4 370 us with the host's, 496 with the GPU's; 32 526
+// and 704; 48 788 and 814; 64 1,737 and 1,061).  Beyond, the GPU with the
+// round-robin order of pivots.
 //
 // A sweep is m - 1 steps; a step rotates m / 2 disjoint pairs (p, q), so its
 // rotations are independent and the matrix falls into 2 x 2 blocks, each
@@ -32,6 +37,7 @@ namespace finger {
 
 namespace {
 
+constexpr int kHostDim = 48;      // largest m solved on the host
 constexpr int kLdsDim = 140;      // largest m whose matrix fits one CU's LDS
 constexpr int kMaxSweeps = 60;
 constexpr int kTile = 32;         // pairs per tile side of a large step
@@ -242,10 +248,44 @@ __global__ void __launch_bounds__(256) k_jacobi_rows(double* V, int m, const dou
   for (int i = threadIdx.x; i < m; i += blockDim.x) row[i] = v[i];
 }
 
-}  // namespace
+// A (m x m, row-major): the eigenvalues on its diagonal on return; V: the
+// eigenvectors in its columns.
+void jacobi_host(double* A, int m, double* V) {
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < m; ++j) V[i * m + j] = i == j ? 1.0 : 0.0;
+  // symmetrize exactly
+  for (int i = 0; i < m; ++i)
+    for (int j = i + 1; j < m; ++j) A[i * m + j] = A[j * m + i] = 0.5 * (A[i * m + j] + A[j * m + i]);
+  double total = 0.0;
+  for (int i = 0; i < m * m; ++i) total += A[i] * A[i];
+  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+    double off = 0.0;
+    for (int p = 0; p < m; ++p)
+      for (int q = p + 1; q < m; ++q) off += A[p * m + q] * A[p * m + q];
+    if (off <= 1e-30 * total || off == 0.0) break;
+    for (int p = 0; p < m - 1; ++p) {
+      for (int q = p + 1; q < m; ++q) {
+        const double apq = A[p * m + q];
+        if (apq == 0.0) continue;
+        const double theta = (A[q * m + q] - A[p * m + p]) / (2.0 * apq);
+        const double t = (theta >= 0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
+        const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
+        auto turn = [&](double& x, double& y) {
+          const double x0 = x, y0 = y;
+          x = c * x0 - s * y0;
+          y = s * x0 + c * y0;
+        };
+        for (int k = 0; k < m; ++k) turn(A[k * m + p], A[k * m + q]);  // A <- A J
+        for (int k = 0; k < m; ++k) turn(A[p * m + k], A[q * m + k]);  // A <- J^T A
+        A[p * m + q] = A[q * m + p] = 0.0;
+        for (int k = 0; k < m; ++k) turn(V[k * m + p], V[k * m + q]);  // V <- V J
+      }
+    }
+  }
+}
 
-// m even (every supported length is a multiple of 4)
-int eigh_jacobi(const double* M_dev, int m, double* evals, double* Vout, hipStream_t s) {
+// the same on the GPU
+int jacobi_device(const double* M_dev, int m, double* Ah, double* Vh, hipStream_t s) {
   using namespace abi;
   const size_t mm = (size_t)m * m;
   const int h = m / 2;
@@ -285,6 +325,18 @@ int eigh_jacobi(const double* M_dev, int m, double* evals, double* Vout, hipStre
                        V.p, m, rot.p);
     HIPCHK(hipGetLastError());
   }
+  HIPCHK(hipMemcpyAsync(Ah, cur, mm * 8, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(Vh, V.p, mm * 8, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  return FINGER_OK;
+}
+
+}  // namespace
+
+// m even (every supported length is a multiple of 4)
+int eigh_jacobi(const double* M_dev, int m, double* evals, double* Vout, hipStream_t s) {
+  using namespace abi;
+  const size_t mm = (size_t)m * m;
   std::vector<double> Ah, Vh;
   std::vector<int> order;
   try {
@@ -294,9 +346,14 @@ int eigh_jacobi(const double* M_dev, int m, double* evals, double* Vout, hipStre
   } catch (const std::bad_alloc&) {
     return fail(FINGER_ENOMEM, "host copy of the eigenvectors");
   }
-  HIPCHK(hipMemcpyAsync(Ah.data(), cur, mm * 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(Vh.data(), V.p, mm * 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  if (m <= kHostDim) {
+    HIPCHK(hipMemcpyAsync(Ah.data(), M_dev, mm * 8, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    jacobi_host(Ah.data(), m, Vh.data());
+  } else {
+    const int st = jacobi_device(M_dev, m, Ah.data(), Vh.data(), s);
+    if (st != FINGER_OK) return st;
+  }
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int b) { return Ah[(size_t)a * m + a] > Ah[(size_t)b * m + b]; });
