@@ -631,8 +631,11 @@ __global__ void __launch_bounds__(256) k_knn_select(SelectArgs a) {
 
 // Per query one block of four waves: the candidates' exact distances by
 // direct float32 differences (four candidates in flight per wave), then the
-// best k by (d2, id).  A flagged row scans every point instead, keeping the k
-// best of each wave's share (rare: see the top of the file).
+// best k by (d2, id).  A flagged row then scans every point, eight in flight
+// per wave, and ranks those below the k-th distance known so far (rare: see
+// the top of the file).  Ten such rows x 300,000 x 128 take 15 ms (97 with the
+// points one after another and every slab ranked whole), bounded by the
+// latency of one workgroup's loads; ten rows that are not flagged 0.15.
 struct FinalArgs {
   const float *q, *x;
   const double *qinv, *xinv;  // angular: reciprocal norms
@@ -660,6 +663,31 @@ __device__ __forceinline__ float knn_term(const FinalArgs& a, float q, float x, 
   return __builtin_fmaf(u, u, d);
 }
 
+// Eight wave sums at once: lane l gets that of v[sum8_index(l)], by the
+// additions of wave_sum (each step adds the same two partial sums, and splits
+// the values between the two lanes that did).
+__device__ __forceinline__ int sum8_index(int l) { return ((l & 1) << 2) | (l & 2) | ((l >> 2) & 1); }
+__device__ __forceinline__ float sum8(float (&v)[8]) {
+  constexpr int kDppXor3 = 0x1B, kDppRor8 = 0x128;
+  const int l = lane_id();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const bool up = (l & 1) != 0;
+    v[j] = (up ? v[j + 4] : v[j]) + dpp_f<kDppXor1>(up ? v[j] : v[j + 4]);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const bool up = (l & 2) != 0;
+    v[j] = (up ? v[j + 2] : v[j]) + dpp_f<kDppXor2>(up ? v[j] : v[j + 2]);
+  }
+  const bool up = (l & 4) != 0;
+  // (half mirror, then reversed quads: lane l ^ 4)
+  float s = (up ? v[1] : v[0]) + dpp_f<kDppXor3>(dpp_f<kDppHalfMirror>(up ? v[0] : v[1]));
+  s += dpp_f<kDppRor8>(s);
+  s += shfl_xor_f(s, 16);
+  return s + shfl_xor_f(s, 32);
+}
+
 __global__ void __launch_bounds__(256) k_knn_final(FinalArgs a) {
   extern __shared__ __align__(16) char smem[];
   uint64_t* ex = reinterpret_cast<uint64_t*>(smem);  // [KK], or [2 k + 256] for a flagged row
@@ -671,62 +699,100 @@ __global__ void __launch_bounds__(256) k_knn_final(FinalArgs a) {
     const uint64_t tk = a.over[row] == 0 ? a.tauk[row] : ~0ull;
     a.bound[q] = make_float2(tk == ~0ull ? __int_as_float(0x7f800000) : order_bits_inv((uint32_t)(tk >> 32)), a.qn[q]);
   }
-  int keep;
-  if (a.over[row] == 0) {
-    const uint64_t* best = a.best + row * a.KK;
-    for (int c0 = 4 * w; c0 < a.KK; c0 += 16) {
-      const float* xv[4];
-      double xi[4] = {1.0, 1.0, 1.0, 1.0};
-      int id[4];
-      float d[4] = {0.f, 0.f, 0.f, 0.f};
+  const uint64_t* best = a.best + row * a.KK;
+  for (int c0 = 4 * w; c0 < a.KK; c0 += 16) {
+    const float* xv[4];
+    double xi[4] = {1.0, 1.0, 1.0, 1.0};
+    int id[4];
+    float d[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint64_t key = c0 + e < a.KK ? best[c0 + e] : ~0ull;
-        id[e] = uniform_i(key == ~0ull ? -1 : key_id(key));
-        xv[e] = a.x + (int64_t)(id[e] < 0 ? 0 : id[e]) * a.m;
-        if (a.xinv != nullptr) xi[e] = a.xinv[id[e] < 0 ? 0 : id[e]];
-      }
-      for (int j = l; j < a.m; j += 64) {
-        const float qj = qv[j];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) d[e] = knn_term(a, qj, xv[e][j], qi, xi[e], d[e]);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float s = wave_sum(d[e]);
-        if (l == 0 && c0 + e < a.KK) ex[c0 + e] = id[e] < 0 ? ~0ull : make_key(s, id[e]);
-      }
+    for (int e = 0; e < 4; ++e) {
+      const uint64_t key = c0 + e < a.KK ? best[c0 + e] : ~0ull;
+      id[e] = uniform_i(key == ~0ull ? -1 : key_id(key));
+      xv[e] = a.x + (int64_t)(id[e] < 0 ? 0 : id[e]) * a.m;
+      if (a.xinv != nullptr) xi[e] = a.xinv[id[e] < 0 ? 0 : id[e]];
     }
+    for (int j = l; j < a.m; j += 64) {
+      const float qj = qv[j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] = knn_term(a, qj, xv[e][j], qi, xi[e], d[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float s = wave_sum(d[e]);
+      if (l == 0 && c0 + e < a.KK) ex[c0 + e] = id[e] < 0 ? ~0ull : make_key(s, id[e]);
+    }
+  }
+  __syncthreads();
+  int keep = a.KK;
+  if (a.over[row] != 0) {
+    // the candidates only give the bound: they are met again among all points
+    __shared__ uint64_t s_bound;
+    __shared__ int s_cnt;
+    for (int i = t; i < a.KK; i += 256) {
+      const uint64_t v = ex[i];
+      int rk = 0;
+      for (int o = 0; o < a.KK; ++o) rk += (ex[o] < v || (ex[o] == v && o < i)) ? 1 : 0;
+      if (rk == a.k - 1) s_bound = v;
+    }
+    if (t == 0) s_cnt = 0;
     __syncthreads();
-    keep = a.KK;
-  } else {
-    // slabs of 256 points appended after the best k so far, then ranked
-    uint64_t* list = ex;                 // [k] ascending
-    uint64_t* slab = ex + a.k;           // [256]
-    uint64_t* next = slab + 256;         // [k]
+    uint64_t bound = s_bound;
+    uint64_t* list = ex;        // [k] ascending
+    uint64_t* slab = ex + a.k;  // [256] keys up to the bound among 256 points
+    uint64_t* next = slab + 256;  // [k]
     for (int i = t; i < a.k; i += 256) list[i] = ~0ull;
     for (int64_t b0 = 0; b0 < a.n; b0 += 256) {
-      for (int e = w; e < 256; e += 4) {
-        const int64_t id = b0 + e;
-        uint64_t key = ~0ull;
-        if (id < a.n && knn_allowed(a.f, q, (int32_t)id)) {
-          const float* xv = a.x + id * a.m;
-          const double xi = a.xinv != nullptr ? a.xinv[id] : 1.0;
-          float d = 0.f;
-          for (int j = l; j < a.m; j += 64) d = knn_term(a, qv[j], xv[j], qi, xi, d);
-          key = make_key(wave_sum(d), (int)id);
+      for (int e0 = 0; e0 < 64; e0 += 8) {
+        const int64_t first = b0 + 64 * w + e0;
+        const float* xv[8];
+        double xi[8];
+        float d[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int64_t id = first + e < a.n ? first + e : a.n - 1;
+          xv[e] = a.x + id * a.m;
+          xi[e] = a.xinv != nullptr ? a.xinv[id] : 1.0;
+          d[e] = 0.f;
         }
-        if (l == 0) slab[e] = key;
+        for (int j = l; j < a.m; j += 128) {
+          // (both strides' loads together; the sum runs over the strides in order)
+          const int j2 = j + 64 < a.m ? j + 64 : j;
+          const float q1 = qv[j], q2 = qv[j2];
+          float x1[8], x2[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            x1[e] = xv[e][j];
+            x2[e] = xv[e][j2];
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            d[e] = knn_term(a, q1, x1[e], qi, xi[e], d[e]);
+            const float d2 = knn_term(a, q2, x2[e], qi, xi[e], d[e]);
+            d[e] = j2 != j ? d2 : d[e];
+          }
+        }
+        const float mine = sum8(d);
+        const int64_t id = first + sum8_index(l);
+        if (l < 8 && id < a.n) {
+          const uint64_t key = make_key(mine, (int)id);
+          if (key <= bound && knn_allowed(a.f, q, (int32_t)id)) slab[atomicAdd(&s_cnt, 1)] = key;
+        }
       }
       __syncthreads();
-      for (int i = t; i < a.k + 256; i += 256) {
-        const uint64_t key = list[i];
-        int rk = 0;
-        for (int o = 0; o < a.k + 256; ++o) rk += (list[o] < key || (list[o] == key && o < i)) ? 1 : 0;
-        if (rk < a.k) next[rk] = key;
+      const int total = a.k + s_cnt;
+      if (total > a.k) {
+        for (int i = t; i < total; i += 256) {
+          const uint64_t key = list[i];
+          int rk = 0;
+          for (int o = 0; o < total; ++o) rk += (list[o] < key || (list[o] == key && o < i)) ? 1 : 0;
+          if (rk < a.k) next[rk] = key;
+        }
+        __syncthreads();
+        for (int i = t; i < a.k; i += 256) list[i] = next[i];
+        bound = min(bound, next[a.k - 1]);
+        if (t == 0) s_cnt = 0;
       }
-      __syncthreads();
-      for (int i = t; i < a.k; i += 256) list[i] = next[i];
       __syncthreads();
     }
     keep = a.k;
