@@ -635,7 +635,7 @@ __global__ void __launch_bounds__(256) k_knn_select(SelectArgs a) {
 // per wave, and ranks those below the k-th distance known so far (rare: see
 // the top of the file).  Ten such rows x 300,000 x 128 take 15 ms (97 with the
 // points one after another and every slab ranked whole), bounded by the
-// latency of one workgroup's loads; ten rows that are not flagged 0.15.
+// latency of one workgroup's loads.
 struct FinalArgs {
   const float *q, *x;
   const double *qinv, *xinv;  // angular: reciprocal norms
@@ -646,9 +646,6 @@ struct FinalArgs {
   KnnFilter f;
   int32_t* ids;
   float* dist;
-  const uint64_t* tauk;
-  const float* qn;
-  float2* bound;  // see launch_exact_knn (may be NULL)
 };
 
 __device__ __forceinline__ float knn_term(const FinalArgs& a, float q, float x, double qi, double xi, float d) {
@@ -688,6 +685,69 @@ __device__ __forceinline__ float sum8(float (&v)[8]) {
   return s + shfl_xor_f(s, 32);
 }
 
+// A flagged row: the k smallest keys of all points to ex[0 .. k).  ex holds the
+// candidates' KK exact keys, which only give the first bound (they are met
+// again among the points); room for 2 k + 256 keys.
+__device__ __forceinline__ void search_all(const FinalArgs& a, int64_t q, uint64_t* ex) {
+  const int t = threadIdx.x, w = uniform_i(t >> 6), l = t & 63;
+  const float* qv = a.q + q * a.m;
+  const double qi = a.qinv != nullptr ? a.qinv[q] : 1.0;
+  __shared__ uint64_t s_bound;
+  __shared__ int s_cnt;
+  for (int i = t; i < a.KK; i += 256) {
+    const uint64_t v = ex[i];
+    int rk = 0;
+    for (int o = 0; o < a.KK; ++o) rk += (ex[o] < v || (ex[o] == v && o < i)) ? 1 : 0;
+    if (rk == a.k - 1) s_bound = v;
+  }
+  if (t == 0) s_cnt = 0;
+  __syncthreads();
+  uint64_t bound = s_bound;
+  uint64_t* list = ex;        // [k] ascending
+  uint64_t* slab = ex + a.k;  // [256] keys up to the bound among 256 points
+  uint64_t* next = slab + 256;  // [k]
+  for (int i = t; i < a.k; i += 256) list[i] = ~0ull;
+  for (int64_t b0 = 0; b0 < a.n; b0 += 256) {
+    for (int e0 = 0; e0 < 64; e0 += 8) {
+      const int64_t first = b0 + 64 * w + e0;
+      if (first >= a.n) break;
+      const int last = (int)min(a.n - 1 - first, (int64_t)7);
+      const float* x0 = a.x + first * a.m;
+      float d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      for (int j = l; j < a.m; j += 64) {
+        const float qj = qv[j];
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = x0[min(e, last) * a.m + j];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          d[e] = knn_term(a, qj, x[e], qi, a.xinv != nullptr ? a.xinv[first + min(e, last)] : 1.0, d[e]);
+      }
+      const float mine = sum8(d);
+      const int64_t id = first + sum8_index(l);
+      if (l < 8 && id < a.n) {
+        const uint64_t key = make_key(mine, (int)id);
+        if (key <= bound && knn_allowed(a.f, q, (int32_t)id)) slab[atomicAdd(&s_cnt, 1)] = key;
+      }
+    }
+    __syncthreads();
+    const int total = a.k + s_cnt;
+    if (total > a.k) {
+      for (int i = t; i < total; i += 256) {
+        const uint64_t key = list[i];
+        int rk = 0;
+        for (int o = 0; o < total; ++o) rk += (list[o] < key || (list[o] == key && o < i)) ? 1 : 0;
+        if (rk < a.k) next[rk] = key;
+      }
+      __syncthreads();
+      for (int i = t; i < a.k; i += 256) list[i] = next[i];
+      bound = min(bound, next[a.k - 1]);
+      if (t == 0) s_cnt = 0;
+    }
+    __syncthreads();
+  }
+}
+
 __global__ void __launch_bounds__(256) k_knn_final(FinalArgs a) {
   extern __shared__ __align__(16) char smem[];
   uint64_t* ex = reinterpret_cast<uint64_t*>(smem);  // [KK], or [2 k + 256] for a flagged row
@@ -695,10 +755,7 @@ __global__ void __launch_bounds__(256) k_knn_final(FinalArgs a) {
   const int64_t row = blockIdx.x, q = a.row0 + row;
   const float* qv = a.q + q * a.m;
   const double qi = a.qinv != nullptr ? a.qinv[q] : 1.0;
-  if (a.bound != nullptr && t == 0) {
-    const uint64_t tk = a.over[row] == 0 ? a.tauk[row] : ~0ull;
-    a.bound[q] = make_float2(tk == ~0ull ? __int_as_float(0x7f800000) : order_bits_inv((uint32_t)(tk >> 32)), a.qn[q]);
-  }
+  const bool flagged = a.over[row] != 0;
   const uint64_t* best = a.best + row * a.KK;
   for (int c0 = 4 * w; c0 < a.KK; c0 += 16) {
     const float* xv[4];
@@ -725,76 +782,8 @@ __global__ void __launch_bounds__(256) k_knn_final(FinalArgs a) {
   }
   __syncthreads();
   int keep = a.KK;
-  if (a.over[row] != 0) {
-    // the candidates only give the bound: they are met again among all points
-    __shared__ uint64_t s_bound;
-    __shared__ int s_cnt;
-    for (int i = t; i < a.KK; i += 256) {
-      const uint64_t v = ex[i];
-      int rk = 0;
-      for (int o = 0; o < a.KK; ++o) rk += (ex[o] < v || (ex[o] == v && o < i)) ? 1 : 0;
-      if (rk == a.k - 1) s_bound = v;
-    }
-    if (t == 0) s_cnt = 0;
-    __syncthreads();
-    uint64_t bound = s_bound;
-    uint64_t* list = ex;        // [k] ascending
-    uint64_t* slab = ex + a.k;  // [256] keys up to the bound among 256 points
-    uint64_t* next = slab + 256;  // [k]
-    for (int i = t; i < a.k; i += 256) list[i] = ~0ull;
-    for (int64_t b0 = 0; b0 < a.n; b0 += 256) {
-      for (int e0 = 0; e0 < 64; e0 += 8) {
-        const int64_t first = b0 + 64 * w + e0;
-        const float* xv[8];
-        double xi[8];
-        float d[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int64_t id = first + e < a.n ? first + e : a.n - 1;
-          xv[e] = a.x + id * a.m;
-          xi[e] = a.xinv != nullptr ? a.xinv[id] : 1.0;
-          d[e] = 0.f;
-        }
-        for (int j = l; j < a.m; j += 128) {
-          // (both strides' loads together; the sum runs over the strides in order)
-          const int j2 = j + 64 < a.m ? j + 64 : j;
-          const float q1 = qv[j], q2 = qv[j2];
-          float x1[8], x2[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            x1[e] = xv[e][j];
-            x2[e] = xv[e][j2];
-          }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            d[e] = knn_term(a, q1, x1[e], qi, xi[e], d[e]);
-            const float d2 = knn_term(a, q2, x2[e], qi, xi[e], d[e]);
-            d[e] = j2 != j ? d2 : d[e];
-          }
-        }
-        const float mine = sum8(d);
-        const int64_t id = first + sum8_index(l);
-        if (l < 8 && id < a.n) {
-          const uint64_t key = make_key(mine, (int)id);
-          if (key <= bound && knn_allowed(a.f, q, (int32_t)id)) slab[atomicAdd(&s_cnt, 1)] = key;
-        }
-      }
-      __syncthreads();
-      const int total = a.k + s_cnt;
-      if (total > a.k) {
-        for (int i = t; i < total; i += 256) {
-          const uint64_t key = list[i];
-          int rk = 0;
-          for (int o = 0; o < total; ++o) rk += (list[o] < key || (list[o] == key && o < i)) ? 1 : 0;
-          if (rk < a.k) next[rk] = key;
-        }
-        __syncthreads();
-        for (int i = t; i < a.k; i += 256) list[i] = next[i];
-        bound = min(bound, next[a.k - 1]);
-        if (t == 0) s_cnt = 0;
-      }
-      __syncthreads();
-    }
+  if (flagged) {
+    search_all(a, q, ex);
     keep = a.k;
   }
   for (int i = t; i < keep; i += 256) {
@@ -806,6 +795,14 @@ __global__ void __launch_bounds__(256) k_knn_final(FinalArgs a) {
       a.dist[q * a.k + rk] = v == ~0ull ? __int_as_float(0x7f800000) : key_d2(v);
     }
   }
+}
+
+// bound[i]: see launch_exact_knn.  (In k_knn_final it cost that 9 us of 43.)
+__global__ void k_knn_bounds(const uint64_t* tauk, const int32_t* over, const float* qn, int64_t rows, float2* bound) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= rows) return;
+  const uint64_t tk = over[i] == 0 ? tauk[i] : ~0ull;
+  bound[i] = make_float2(tk == ~0ull ? __int_as_float(0x7f800000) : order_bits_inv((uint32_t)(tk >> 32)), qn[i]);
 }
 
 // ------------------------------------------------------------------ plan
@@ -1057,10 +1054,10 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
     f.f = c.f;
     f.ids = ids;
     f.dist = dist;
-    f.tauk = v.tauk;
-    f.qn = qn;
-    f.bound = bound;
     hipLaunchKernelGGL(k_knn_final, dim3((unsigned)rows), dim3(256), fin_lds, s, f);
+    if (bound != nullptr)
+      hipLaunchKernelGGL(k_knn_bounds, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, v.tauk, v.over, qn + r0, rows,
+                         bound + r0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
