@@ -44,13 +44,15 @@ inline int ok() {
     if (e_ != hipSuccess) return fail(FINGER_EDEVICE, "%s: %s", #x, hipGetErrorString(e_)); \
   } while (0)
 
-// Allocation with an injectable failure (FINGER_FAULT_INJECT=alloc makes
-// every allocation fail, to test the error path).
+// Allocation with an injectable failure, to test the error paths:
+// FINGER_FAULT_INJECT=alloc makes every allocation fail, alloc:BYTES those of
+// more than BYTES.
 inline int dev_alloc(void** p, size_t bytes, const char* what) {
   *p = nullptr;
   if (bytes == 0) return FINGER_OK;
   const char* fi = std::getenv("FINGER_FAULT_INJECT");
-  if (fi != nullptr && std::strcmp(fi, "alloc") == 0)
+  if (fi != nullptr && (std::strcmp(fi, "alloc") == 0 ||
+                        (std::strncmp(fi, "alloc:", 6) == 0 && bytes > std::strtoull(fi + 6, nullptr, 10))))
     return fail(FINGER_ENOMEM, "allocation of %zu bytes for %s failed (injected)", bytes, what);
   hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {

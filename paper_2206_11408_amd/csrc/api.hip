@@ -710,7 +710,8 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
   finger_graph_stats st{};
   int rc = FINGER_OK;
   auto alloc = [&](auto& buf, size_t bytes, const char* what) {
-    if (rc == FINGER_OK) rc = dev_alloc(reinterpret_cast<void**>(&buf.p), std::max<size_t>(bytes, 4), what);
+    if (rc == FINGER_OK && buf.p == nullptr)
+      rc = dev_alloc(reinterpret_cast<void**>(&buf.p), std::max<size_t>(bytes, 4), what);
   };
 
   // 1. kNN (k + 1 with the point itself, which is then dropped)
@@ -728,17 +729,31 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
   DevBuf<char> kws;
   DevBuf<int32_t> ids1, ids;
   DevBuf<float> d1, dk;
-  const size_t kws_bytes = exact_knn_ws_bytes(groups != nullptr ? gmax : n, m, batch, k1);
-  alloc(kws, kws_bytes, "kNN workspace");
+  // the kNN's workspace last: a small one does where the usual one does not fit
+  KnnSpace space;
+  space.angular = false;  // the points are normalized already
+  size_t kws_bytes = 0;
+  auto alloc_knn = [&](DevBuf<char>& buf, int64_t points, int64_t rows, int kk, bool small) {
+    space.small = small;
+    kws_bytes = exact_knn_ws_bytes(points, m, rows, kk, space);
+    alloc(buf, kws_bytes, "kNN workspace");
+  };
   alloc(ids1, (size_t)batch * k1 * 4, "kNN ids");
   alloc(d1, (size_t)batch * k1 * 4, "kNN distances");
   alloc(ids, (size_t)nk * 4, "kNN lists");
   alloc(dk, (size_t)nk * 4, "kNN list distances");
   if (rc != FINGER_OK) return rc;
+  for (const bool small : {false, true}) {
+    rc = FINGER_OK;
+    alloc_knn(kws, groups != nullptr ? gmax : n, batch, k1, small);
+    if (rc != FINGER_ENOMEM) break;
+  }
+  if (rc != FINGER_OK) return rc;
   if (groups == nullptr) {
     for (int64_t b0 = 0; b0 < n; b0 += batch) {
       const int64_t nb = std::min(batch, n - b0);
-      HIPCHK(launch_exact_knn(X, n, m, X + b0 * m, nb, k1, FINGER_L2, ids1.p, d1.p, kws.p, kws_bytes, s));
+      HIPCHK(launch_exact_knn(X, n, m, X + b0 * m, nb, k1, FINGER_L2, ids1.p, d1.p, kws.p, kws_bytes, s, nullptr,
+                              nullptr, space));
       HIPCHK(launch_drop_self(ids1.p, d1.p, nb, k1, k, ids.p + b0 * k, dk.p + b0 * k, b0, 0, s));
       HIPCHK(hipStreamSynchronize(s));
       if (progress) progress("knn", b0 + nb, n, progress_user);
@@ -748,7 +763,8 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
       const int64_t o = groups[g], ng = groups[g + 1] - groups[g];
       for (int64_t b0 = 0; b0 < ng; b0 += batch) {
         const int64_t nb = std::min(batch, ng - b0);
-        HIPCHK(launch_exact_knn(X + o * m, ng, m, X + (o + b0) * m, nb, k1, FINGER_L2, ids1.p, d1.p, kws.p, kws_bytes, s));
+        HIPCHK(launch_exact_knn(X + o * m, ng, m, X + (o + b0) * m, nb, k1, FINGER_L2, ids1.p, d1.p, kws.p, kws_bytes, s, nullptr,
+                              nullptr, space));
         HIPCHK(launch_drop_self(ids1.p, d1.p, nb, k1, k, ids.p + (o + b0) * k, dk.p + (o + b0) * k, b0, o, s));
       }
       if ((g + 1) % 1024 == 0 || g + 1 == n_groups) {
@@ -834,14 +850,37 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
   t0 = now();
   DevBuf<int32_t> deg, fa, fb;
   DevBuf<uint32_t> label, stamp, counts;
-  alloc(deg, (size_t)n * 4, "degrees");
-  alloc(fa, (size_t)n * 4, "label frontier");
-  alloc(fb, (size_t)n * 4, "label frontier");
-  alloc(label, (size_t)n * 4, "labels");
-  alloc(stamp, (size_t)n * 4, "label stamps");
+  // what the repair does not read of the steps before, where it needs the room
+  auto free_edges = [&] {
+    ka.reset();
+    va.reset();
+    vb.reset();
+    k2a.reset();
+    k2b.reset();
+    cnt.reset();
+    indptr.reset();
+    ids.reset();
+    dk.reset();
+    nbr.reset();
+    nd.reset();
+  };
+  auto alloc_all = [&](auto&& group) {
+    group();
+    if (rc != FINGER_ENOMEM) return;
+    free_edges();
+    rc = FINGER_OK;
+    group();
+  };
   constexpr int kSweeps = 8;   // label sweeps between two looks at the frontier
   constexpr int kBatches = 8;  // looks before a graph counts as one of long paths
-  alloc(counts, (kSweeps + 2) * 4, "frontier sizes");
+  alloc_all([&] {
+    alloc(deg, (size_t)n * 4, "degrees");
+    alloc(fa, (size_t)n * 4, "label frontier");
+    alloc(fb, (size_t)n * 4, "label frontier");
+    alloc(label, (size_t)n * 4, "labels");
+    alloc(stamp, (size_t)n * 4, "label stamps");
+    alloc(counts, (kSweeps + 2) * 4, "frontier sizes");
+  });
   if (rc != FINGER_OK) return rc;
   HIPCHK(launch_degrees(out_graph, n, W, deg.p, s));
   HIPCHK(launch_label_init(n, entry, label.p, stamp.p, s));
@@ -886,7 +925,7 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
   }
   // start nodes in id order (stamp: flags, then ka/kb's sums: positions)
   DevBuf<uint32_t> free_label;
-  alloc(free_label, (size_t)n * 4, "labels with a free slot");
+  alloc_all([&] { alloc(free_label, (size_t)n * 4, "labels with a free slot"); });
   if (rc != FINGER_OK) return rc;
   HIPCHK(launch_root_flags(n, label.p, deg.p, W, stamp.p, free_label.p, s));
   tb = tbytes;
@@ -902,19 +941,33 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
     HIPCHK(launch_root_list(n, stamp.p, kb.p, fa.p, s));
     constexpr int J = 16;  // nearest reached nodes listed per start node
     const int j = (int)std::min<int64_t>(J, n), per = W + 4 + 3 * j;
-    const int64_t rb = std::min<int64_t>(roots, 65536);
     DevBuf<float> rq, rd, rdist;
     DevBuf<float2> rb_bound;
     DevBuf<int32_t> rid, rinfo;
     DevBuf<char> rws;
-    const size_t rws_bytes = exact_knn_ws_bytes(n, m, rb, j);
-    alloc(rq, (size_t)rb * m * 4, "start nodes");
-    alloc(rd, (size_t)rb * j * 4, "nearest distances");
-    alloc(rid, (size_t)rb * j * 4, "nearest ids");
-    alloc(rdist, (size_t)rb * j * 4, "nearest distances");
-    alloc(rb_bound, (size_t)rb * 8, "nearest bounds");
-    alloc(rinfo, (size_t)rb * per * 4, "repair rows");
-    alloc(rws, rws_bytes, "kNN workspace");
+    int64_t rb = 0;
+    // (a small workspace, then fewer start nodes at a time, where there is no
+    // room for more)
+    for (const int tight : {0, 1, 2}) {
+      rc = FINGER_OK;
+      rb = std::min<int64_t>(roots, tight < 2 ? 65536 : 4096);
+      alloc_all([&] {
+        alloc(rq, (size_t)rb * m * 4, "start nodes");
+        alloc(rd, (size_t)rb * j * 4, "nearest distances");
+        alloc(rid, (size_t)rb * j * 4, "nearest ids");
+        alloc(rdist, (size_t)rb * j * 4, "nearest distances");
+        alloc(rb_bound, (size_t)rb * 8, "nearest bounds");
+        alloc(rinfo, (size_t)rb * per * 4, "repair rows");
+        alloc_knn(rws, n, rb, j, tight > 0);
+      });
+      if (rc != FINGER_ENOMEM) break;
+      rq.reset();
+      rd.reset();
+      rid.reset();
+      rdist.reset();
+      rb_bound.reset();
+      rinfo.reset();
+    }
     if (rc != FINGER_OK) return rc;
     std::vector<int32_t> root_h, info;
     std::vector<int64_t> at;
@@ -941,8 +994,8 @@ int build_graph_impl(const float* data, int64_t n, int32_t m, int32_t knn_k, int
         const int64_t nr = std::min(rb, roots - r0);
         const KnnFilter filter{free_label.p, fa.p + r0};
         HIPCHK(launch_gather_rows(X, m, fa.p + r0, nr, rq.p, s));
-        HIPCHK(launch_exact_knn(X, n, m, rq.p, nr, j, FINGER_L2, rid.p, rd.p, rws.p, rws_bytes, s, &filter,
-                                rb_bound.p));
+        HIPCHK(launch_exact_knn(X, n, m, rq.p, nr, j, FINGER_L2, rid.p, rd.p, rws.p, kws_bytes, s, &filter,
+                                rb_bound.p, space));
         HIPCHK(launch_repair_gather(X, m, out_graph, W, deg.p, fa.p + r0, nr, rid.p, rd.p, rb_bound.p, j, rdist.p,
                                     rinfo.p, s));
         HIPCHK(hipMemcpyAsync(info.data(), rinfo.p, (size_t)nr * per * 4, hipMemcpyDeviceToHost, s));

@@ -244,8 +244,14 @@ hipError_t launch_gather_rows(const float* X, int m, const int32_t* ids, int64_t
 hipError_t launch_check_ids(const int32_t* ids, int64_t cnt, int64_t n, int32_t* bad,
                             hipStream_t s);
 
-// exact kNN (knn.hip); the workspace never shrinks as n or nq grows
-size_t exact_knn_ws_bytes(int64_t n, int m, int64_t nq, int k);
+// exact kNN (knn.hip); the workspace never shrinks as n or nq grows, and past
+// about 1.8 GB (k up to 48; 0.15 where it is to be small) grows by 4 bytes a
+// point, with angular 12 a point and 8 a query
+struct KnnSpace {
+  bool angular = true;  // room for the angular metric's norms
+  bool small = false;   // smaller batches: slower by their launches
+};
+size_t exact_knn_ws_bytes(int64_t n, int m, int64_t nq, int k, const KnnSpace& space = {});
 // restriction of a kNN call: query i takes only points x with
 // point_label[x] < row_id[i] + 1
 struct KnnFilter {
@@ -255,7 +261,7 @@ struct KnnFilter {
 hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q, int64_t nq,
                             int k, int metric, int32_t* ids, float* dist, void* ws,
                             size_t ws_bytes, hipStream_t s, const KnnFilter* filter = nullptr,
-                            float2* bound = nullptr);
+                            float2* bound = nullptr, const KnnSpace& space = {});
 // bound[i] of the call above: (no candidate score of a point outside the
 // exact re-rank is smaller; infinity if none is outside, |q_i|^2)
 

@@ -50,26 +50,27 @@ constexpr int kKnnGrowth = 5;
 constexpr int kTileQ = 128;                // query rows of a block's tile
 constexpr int kPadX = 128;                 // points are padded to a multiple of this
 constexpr int kBK = 32;                    // k extent of one staged slab
-constexpr int64_t kRowBatch = 65536;       // query rows whose candidates are held at a time
+constexpr int64_t kRowBatch = 65536;       // query rows whose candidates are held at a time, at most
 constexpr int kMaxChunks = 512;
 
 // ------------------------------------------------------------- operands
 
-// Rows of `src` in split precision, 16 lanes per row: hi/lo [rows_pad][kpad]
-// (zero past the data), half the squared norm (norm_scale 0.5; 1 for queries,
-// 0 for the inner product) and, with stride a > 0, row p taken from point
-// p a mod n, whose id goes to perm[p].  inv != NULL: unit-normalized rows, the
+// Positions first .. first + rows_pad of `src` in split precision, 16 lanes
+// per row: hi/lo [rows_pad][kpad] (zero past the data), half the squared norm
+// (norm_scale 0.5; 1 for queries, 0 for the inner product) and, with stride
+// a > 0, position p taken from point p a mod n, whose id goes to perm[p].  inv != NULL: unit-normalized rows, the
 // reciprocal norms written there.  flag is set if any lo is not zero.
-__global__ void __launch_bounds__(256) k_knn_split(const float* __restrict__ src, int64_t n, int m, int64_t rows_pad,
-                                                   int kpad, int64_t a, float norm_scale, float pad_norm,
+__global__ void __launch_bounds__(256) k_knn_split(const float* __restrict__ src, int64_t n, int m, int64_t first,
+                                                   int64_t rows_pad, int kpad, int64_t a, float norm_scale, float pad_norm,
                                                    __bf16* __restrict__ hi, __bf16* __restrict__ lo,
                                                    float* __restrict__ norm, int32_t* __restrict__ perm,
                                                    double* __restrict__ inv, uint32_t* __restrict__ flag) {
   const int lg = threadIdx.x & 15;
   const int64_t p = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   if (p >= rows_pad) return;  // (rows_pad is a multiple of 16: whole blocks)
-  const bool live = p < n;
-  const int64_t id = !live ? 0 : (a > 0 ? (int64_t)(((uint64_t)p * (uint64_t)a) % (uint64_t)n) : p);
+  const int64_t pos = first + p;
+  const bool live = pos < n;
+  const int64_t id = !live ? 0 : (a > 0 ? (int64_t)(((uint64_t)pos * (uint64_t)a) % (uint64_t)n) : pos);
   const float* x = src + id * m;
   double s = 1.0;
   if (inv != nullptr) {
@@ -116,7 +117,7 @@ __global__ void __launch_bounds__(256) k_knn_split(const float* __restrict__ src
   nrm = group_sum<16>(nrm);
   if (lg == 0) {
     norm[p] = live ? norm_scale * nrm : pad_norm;
-    if (perm != nullptr) perm[p] = live ? (int32_t)id : -1;
+    if (perm != nullptr) perm[pos] = live ? (int32_t)id : -1;
   }
   if (ballot(any_lo) != 0ull && (threadIdx.x & 63) == 0 && *flag == 0u) *flag = 1u;
 }
@@ -124,6 +125,8 @@ __global__ void __launch_bounds__(256) k_knn_split(const float* __restrict__ src
 // ---------------------------------------------------------------- scores
 
 struct ScanArgs {
+  // indexed by query row and position; only this batch's rows and this
+  // window's positions are there
   const __bf16 *qh, *ql;    // [q_pad][kpad]
   const __bf16 *xh, *xl;    // [n_pad][kpad]
   const float* qn;          // [q_pad] |q|^2 (0 for the inner product)
@@ -811,7 +814,7 @@ size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
 struct KnnPlan {
   int KK, kpad, prefix, cap, nch;
-  int64_t n_pad, q_pad, rows, stride;
+  int64_t n_pad, q_pad, rows, window, stride;
   size_t off_xh, off_xl, off_qh, off_ql, off_hx, off_qn, off_perm, off_xinv, off_qinv, off_flag, off_best, off_tauk,
       off_ht, off_over, off_counts, off_cand, total;
 };
@@ -821,18 +824,28 @@ struct KnnPlan {
 // the spread of small shares.
 int knn_region(int cap, int nch) { return nch == 1 ? cap : (cap + nch - 1) / nch + 16; }
 
-KnnPlan knn_plan(int64_t n, int m, int64_t nq, int k) {
+// Memory: the planes hold a window of positions at a time (kKnnPlanes bytes
+// at most; with several windows they are split again for every batch of rows:
+// 12 bytes moved per element against 2 x 65,536 operations), and the keys those
+// of kRowBatch rows.  Both are 1/16 of that where the caller asks for a small
+// workspace.  Neither changes a result: the KK smallest keys do not depend on
+// where a phase ends.
+constexpr size_t kKnnPlanes = (size_t)1 << 30;
+
+KnnPlan knn_plan(int64_t n, int m, int64_t nq, int k, const KnnSpace& space) {
+  const int shrink = space.small ? 16 : 1;
   KnnPlan p{};
   p.KK = k + kKnnSlack;
   p.kpad = (m + kBK - 1) / kBK * kBK;
   p.n_pad = (n + kPadX - 1) / kPadX * kPadX;
   p.q_pad = (nq + kTileQ - 1) / kTileQ * kTileQ;
-  p.rows = std::min(p.q_pad, kRowBatch);
   p.cap = std::max(512, 16 * p.KK);
+  p.rows = std::min(p.q_pad, kRowBatch / shrink);
   // prefix scored whole: a few times KK, or everything when little is left
   int64_t prefix = p.KK <= 64 ? 512 : 1024;
   if (n <= 1024) prefix = 1024;
   p.prefix = (int)std::min(prefix, p.n_pad);
+  p.window = std::min(p.n_pad, std::max<int64_t>(1024, (int64_t)(kKnnPlanes / shrink) / (4 * p.kpad) / kPadX * kPadX));
   // chunks of points per row tile: enough blocks (two fit a CU) for several
   // rounds, in whole multiples of the eight XCDs
   const int64_t rowtiles = p.rows / kTileQ, tiles = p.n_pad / kPadX;
@@ -854,15 +867,15 @@ KnnPlan knn_plan(int64_t n, int m, int64_t nq, int k) {
     o += up256(bytes);
     return at;
   };
-  p.off_xh = take((size_t)p.n_pad * p.kpad * 2);
-  p.off_xl = take((size_t)p.n_pad * p.kpad * 2);
-  p.off_qh = take((size_t)p.q_pad * p.kpad * 2);
-  p.off_ql = take((size_t)p.q_pad * p.kpad * 2);
-  p.off_hx = take((size_t)p.n_pad * 4);
-  p.off_qn = take((size_t)p.q_pad * 4);
+  p.off_xh = take((size_t)p.window * p.kpad * 2);
+  p.off_xl = take((size_t)p.window * p.kpad * 2);
+  p.off_qh = take((size_t)p.rows * p.kpad * 2);
+  p.off_ql = take((size_t)p.rows * p.kpad * 2);
+  p.off_hx = take((size_t)p.window * 4);
+  p.off_qn = take((size_t)p.rows * 4);
   p.off_perm = take((size_t)p.n_pad * 4);
-  p.off_xinv = take((size_t)n * 8);
-  p.off_qinv = take((size_t)nq * 8);
+  p.off_xinv = take(space.angular ? (size_t)n * 8 : 0);
+  p.off_qinv = take(space.angular ? (size_t)nq * 8 : 0);
   p.off_flag = take(4);
   p.off_best = take((size_t)p.rows * p.KK * 8);
   p.off_tauk = take((size_t)p.rows * 8);
@@ -892,7 +905,9 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s) {
 
 }  // namespace
 
-size_t exact_knn_ws_bytes(int64_t n, int m, int64_t nq, int k) { return knn_plan(n, m, nq, k).total; }
+size_t exact_knn_ws_bytes(int64_t n, int m, int64_t nq, int k, const KnnSpace& space) {
+  return knn_plan(n, m, nq, k, space).total;
+}
 
 bool knn_certain(float d, float last, float score, float qq, int m) {
   // A float32 distance is a sum of squares with at most 64 roundings on any
@@ -912,10 +927,10 @@ bool knn_certain(float d, float last, float score, float qq, int m) {
 
 hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q, int64_t nq, int k, int metric,
                             int32_t* ids, float* dist, void* ws, size_t ws_bytes, hipStream_t s, const KnnFilter* filter,
-                            float2* bound) {
+                            float2* bound, const KnnSpace& space) {
   if (nq == 0) return hipSuccess;
-  const KnnPlan p = knn_plan(n, m, nq, k);
-  if (ws_bytes < p.total) return hipErrorInvalidValue;
+  const KnnPlan p = knn_plan(n, m, nq, k, space);
+  if (ws_bytes < p.total || (metric == FINGER_ANGULAR && !space.angular)) return hipErrorInvalidValue;
   char* b = static_cast<char*>(ws);
   auto at = [&](size_t off) { return static_cast<void*>(b + off); };
   const bool ang = metric == FINGER_ANGULAR, ip = metric == FINGER_IP;
@@ -929,19 +944,19 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
   // stride of the scan order: near the golden section of n, prime to n
   int64_t a = std::max<int64_t>(1, (int64_t)(0.6180339887498949 * (double)n));
   while (std::gcd(a, n) != 1) ++a;
-  hipLaunchKernelGGL(k_knn_split, dim3((unsigned)(p.n_pad / 16)), dim3(256), 0, s, data, n, m, p.n_pad, p.kpad, a,
-                     ip ? 0.f : 0.5f, __builtin_inff(), xh, xl, hx, perm, xinv, flag);
-  hipLaunchKernelGGL(k_knn_split, dim3((unsigned)(p.q_pad / 16)), dim3(256), 0, s, Q, nq, m, p.q_pad, p.kpad,
-                     (int64_t)0, ip ? 0.f : 1.f, 0.f, qh, ql, qn, (int32_t*)nullptr, qinv, flag);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  auto split_points = [&](int64_t first) {
+    const int64_t rows = std::min(p.window, p.n_pad - first);
+    hipLaunchKernelGGL(k_knn_split, dim3((unsigned)(rows / 16)), dim3(256), 0, s, data, n, m, first, rows, p.kpad, a,
+                       ip ? 0.f : 0.5f, __builtin_inff(), xh, xl, hx, perm, xinv, flag);
+    return hipGetLastError();
+  };
+  auto split_queries = [&](int64_t first, int64_t rows_pad) {
+    hipLaunchKernelGGL(k_knn_split, dim3((unsigned)(rows_pad / 16)), dim3(256), 0, s, Q, nq, m, first, rows_pad, p.kpad,
+                       (int64_t)0, ip ? 0.f : 1.f, 0.f, qh, ql, qn, (int32_t*)nullptr, qinv, flag);
+    return hipGetLastError();
+  };
 
   ScanArgs c{};
-  c.qh = qh;
-  c.ql = ql;
-  c.xh = xh;
-  c.xl = xl;
-  c.qn = qn;
-  c.hx = hx;
   c.perm = perm;
   c.flag = flag;
   c.tauk = (uint64_t*)at(p.off_tauk);
@@ -968,7 +983,6 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
   v.cand = c.cand;
   v.counts = c.counts;
   v.perm = perm;
-  v.qn = qn;
   v.best = (uint64_t*)at(p.off_best);
   v.tauk = (uint64_t*)at(p.off_tauk);
   v.ht = (float*)at(p.off_ht);
@@ -979,7 +993,7 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
   v.prefix = p.prefix;
   v.ip = c.ip;
   // four waves per row while one per row leaves the GPU under two waves a SIMD
-  const bool wide = std::min(nq, kRowBatch) <= 2048;
+  const bool wide = std::min(nq, p.rows) <= 2048;
   const int sel_lds = (wide ? 1 : 4) * 2 * v.cap * 4;
   const void* sel = wide ? reinterpret_cast<const void*>(k_knn_select<4>) : reinterpret_cast<const void*>(k_knn_select<1>);
   e = hipFuncSetAttribute(sel, hipFuncAttributeMaxDynamicSharedMemorySize, sel_lds);
@@ -1005,12 +1019,31 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
     }
     grow = std::pow(f, 1.0 / phases);
   }
-  for (int64_t r0 = 0; r0 < nq; r0 += kRowBatch) {
-    const int64_t rows = std::min(nq - r0, kRowBatch);
+  const int64_t wtiles = p.window / tx;
+  // arrays of which a part is held, as if from index zero
+  auto from = [](auto* held, int64_t index) {
+    return reinterpret_cast<decltype(held)>(reinterpret_cast<uintptr_t>(held) - (uintptr_t)index * sizeof(*held));
+  };
+  int64_t held = -1;  // first position that the planes hold
+  auto hold = [&](int64_t first_pos) {
+    if (held == first_pos) return hipSuccess;
+    held = first_pos;
+    c.xh = from(xh, first_pos * p.kpad);
+    c.xl = from(xl, first_pos * p.kpad);
+    c.hx = from(hx, first_pos);
+    return split_points(first_pos);
+  };
+  for (int64_t r0 = 0; r0 < nq; r0 += p.rows) {
+    const int64_t rows = std::min(nq - r0, p.rows);
     c.row0 = v.row0 = r0;
+    c.qh = from(qh, r0 * p.kpad);
+    c.ql = from(ql, r0 * p.kpad);
+    c.qn = v.qn = from(qn, r0);
     c.rowtiles = (int)((rows + kTileQ - 1) / kTileQ);
     v.rows = rows;
     v.rows_pad = (int64_t)c.rowtiles * kTileQ;
+    if ((e = hold(0)) != hipSuccess) return e;
+    if ((e = split_queries(r0, v.rows_pad)) != hipSuccess) return e;
     c.base = v.base = 1;
     c.tile0 = 0;
     c.tiles = (int)first;
@@ -1023,10 +1056,17 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
     if ((e = select()) != hipSuccess) return e;
     c.base = v.base = 0;
     int64_t done = first;
-    for (int ph = 1; ph <= phases; ++ph) {
+    for (int ph = 1; ph <= phases;) {
       int64_t next = ph == phases ? all_tiles : (int64_t)std::llround((double)first * std::pow(grow, ph));
       next = std::min(std::max(next, done), all_tiles);
-      if (next == done) continue;
+      if (next == done) {
+        ++ph;
+        continue;
+      }
+      // a phase ends with the window
+      const int64_t wfirst = done / wtiles * wtiles;
+      if ((e = hold(wfirst * tx)) != hipSuccess) return e;
+      next = std::min(next, wfirst + wtiles);
       c.tile0 = done;
       c.tiles = (int)(next - done);
       int64_t nch = std::min<int64_t>(p.nch, c.tiles);
@@ -1056,7 +1096,7 @@ hipError_t launch_exact_knn(const float* data, int64_t n, int m, const float* Q,
     f.dist = dist;
     hipLaunchKernelGGL(k_knn_final, dim3((unsigned)rows), dim3(256), fin_lds, s, f);
     if (bound != nullptr)
-      hipLaunchKernelGGL(k_knn_bounds, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, v.tauk, v.over, qn + r0, rows,
+      hipLaunchKernelGGL(k_knn_bounds, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, v.tauk, v.over, qn, rows,
                          bound + r0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
