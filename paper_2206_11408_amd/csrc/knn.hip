@@ -9,8 +9,10 @@
 // to 256), the two products with lo add nothing and are left out.  The scores
 // only choose the KK = k + kKnnSlack candidates that k_knn_final re-ranks by
 // exact float32 differences: a true neighbour is lost only if kKnnSlack others
-// sit within the score error (about 1e-5 relative) of it; integer data up to
-// 256 scores exactly.
+// sit within the score error of it (about 1e-5 of |q||x|).  Integers up to 256
+// score exactly while |x|^2 and |q|^2 are below 2^24 (the sums start at
+// -|x|^2 / 2 in float32): for any such data up to 256 dimensions; beyond, sums
+// of that size are rounded.
 //
 // Selection.  The points are scanned in phases over growing prefixes of a
 // pseudo-random order (position p holds point p a mod n, a near 0.618 n and
@@ -151,23 +153,24 @@ __device__ __forceinline__ bool knn_allowed(const KnnFilter& f, int64_t row, int
 }
 
 // One (row tile, chunk of point tiles) per block of four waves; wave w owns
-// query rows 32 w .. 32 w + 31 against all 128 points of a tile.  The points'
-// slabs (128 x 32 of hi and lo) go through LDS, two buffers deep, one slab
-// ahead in registers; the query fragments stay in registers for kpad = 32 KS
-// <= 128 (KS = 0: they go through LDS as well).  Chunks are dealt so that the
-// blocks of one XCD (every eighth block) walk the same points at the same
-// time with different query rows: a tile is fetched once per XCD and its L2
-// serves the rest.
-// An LDS row is 64 bytes; its 16-byte pieces are placed at piece ^ (row / 2)
-// % 4, so that eight consecutive rows cover every bank once.
+// query rows 32 w .. 32 w + 31 of the tile's 128 against all points of a point
+// tile.  The points' slabs (32 or 64 coordinates of hi and lo) go through LDS,
+// two buffers deep, one slab ahead in registers; the query fragments stay in
+// registers for kpad = 32 KS <= 128 (KS = 0: they go through LDS as well).
+// Chunks are dealt so that the blocks of one XCD (every eighth block) walk the
+// same points at the same time with different query rows: a tile is fetched
+// once per XCD and its L2 serves the rest.
+// An LDS row's 16-byte pieces are placed at piece ^ (row / 2) % 4 (rows of 64
+// bytes) or piece ^ row % 8 (of 128), so that eight consecutive rows cover
+// every bank once.
 // Accumulators start at -|x|^2 / 2, so d2 = |q|^2 - 2 acc and one comparison
-// with ht decides; a wave whose 64 x 64 comparisons all fail (most of them
+// with ht decides; a wave whose comparisons of a tile all fail (most of them
 // after the first phases) goes on to the next tile.
 // Points of a tile for kpad = 32 ks <= 128 (ks = 0: longer vectors): 64, so that
 // three waves fit a SIMD and one wave's comparisons and waits overlap another's
 // products (128 points with two waves take 1.67 ms where 64 with three take
-// 1.53 ms for 10,000 x 300,000 x 128, one product); longer vectors spend their time on the products and take
-// 128, which halves their query traffic.
+// 1.53 ms for 10,000 x 300,000 x 128, one product); longer vectors spend their
+// time on the products and take 128, which halves their query traffic.
 constexpr int tile_x(int ks) { return ks > 0 ? 64 : 128; }
 // 32-wide k steps per slab
 constexpr int slab_steps(int ks, bool lo) { return ks > 0 && !lo && ks % 2 == 0 ? 2 : 1; }
@@ -407,7 +410,9 @@ __device__ __forceinline__ void scan_body(const ScanArgs& a, __bf16* sm, uint64_
 
 // The instance without the lo products needs fewer registers; both are launched
 // and the flag decides on the device which of them works.  Waves per SIMD: as
-// many as the registers allow without spilling in the loop.
+// many as the registers allow without spilling in the products' loop (at 96
+// coordinates with lo, two addresses are kept in scratch and reread where a key
+// is kept: 10,000 x 300,000 x 96 2.0 ms with three waves, 2.2 with two).
 constexpr int scan_waves(int ks, bool lo) { return ks == 0 || (lo && ks == 4) ? 2 : 3; }
 
 template <int KS, bool LO>
@@ -847,8 +852,8 @@ KnnPlan knn_plan(int64_t n, int m, int64_t nq, int k, const KnnSpace& space) {
   if (n <= 1024) prefix = 1024;
   p.prefix = (int)std::min(prefix, p.n_pad);
   p.window = std::min(p.n_pad, std::max<int64_t>(1024, (int64_t)(kKnnPlanes / shrink) / (4 * p.kpad) / kPadX * kPadX));
-  // chunks of points per row tile: enough blocks (two fit a CU) for several
-  // rounds, in whole multiples of the eight XCDs
+  // chunks of points per row tile: enough blocks (two or three fit a CU) for
+  // several rounds, in whole multiples of the eight XCDs
   const int64_t rowtiles = p.rows / kTileQ, tiles = p.n_pad / kPadX;
   int64_t nch = (2048 + rowtiles - 1) / rowtiles;
   nch = std::min<int64_t>({(nch + 7) / 8 * 8, tiles, kMaxChunks});

@@ -446,8 +446,9 @@ __device__ __forceinline__ void load_query(const KArgs& a, const float* query, f
 
 // Squared difference (or, for the inner product, product) of one piece.  The
 // order of its four terms is written out, so that a distance has the same
-// bits in every instance of the kernel: x, y, z, w, and y first where eight
-// lanes of four pieces (or their multiples) cover the vector exactly.
+// bits in every instance of the kernel: x, y, z, w.  At 128, 512 and 2,048
+// dimensions (the pieces of the earliest shapes cover the vector exactly) y
+// goes first: no gain is in it, distances there have always had these bits.
 template <bool YX>
 __device__ __forceinline__ float piece_sq(const float4& q, const float4& x) {
   const float dx = q.x - x.x, dy = q.y - x.y, dz = q.z - x.z, dw = q.w - x.w;
