@@ -465,8 +465,8 @@ __device__ __forceinline__ float piece_prod(const float4& q, const float4& x) {
 // lane by a cross-lane read (no LDS round trip).
 // qv: the query chunks this lane needs, either in registers or (qlds) read
 // from the wave's LDS copy of the query when needed.  EXACT: squared L2 with
-// m = 4 G T4.
-template <int G, int T4, int NP, bool EXACT>
+// m = 4 G T4.  MASK (any other shape): see masked_terms.
+template <int G, int T4, int NP, bool EXACT, bool MASK>
 __device__ __forceinline__ void dists_pass(const KArgs& a, const float4* qv, const float4* qlds,
                                            const int* __restrict__ ids_lds, int cnt, int p0, float& mine) {
   constexpr int NPP = 64 / G;
@@ -508,10 +508,10 @@ __device__ __forceinline__ void dists_pass(const KArgs& a, const float4* qv, con
     }
     return;
   }
-  // Other shapes: every lane loads, with no branch (so that the waits count
-  // exactly and one pass's sums overlap the next pass's loads): slots past
-  // cnt load the first id's vector again, pieces past m reload the last
-  // piece of the vector and are zeroed after the load.
+  // Other shapes: slots past cnt load the first id's vector again; pieces
+  // past m are zeros (a branch around the load), or with MASK the last piece
+  // of the vector and of the query, loaded by every lane with no branch, and
+  // the term masked to zero.
 #pragma unroll
   for (int h = 0; h < NP; ++h) {
     const int ph = p0 + h * NPP + slot;
@@ -520,13 +520,25 @@ __device__ __forceinline__ void dists_pass(const KArgs& a, const float4* qv, con
     for (int t = 0; t < T4; ++t) {
       const int j = lg + G * t;
       const float4 v = x4[j < a.m4 ? j : a.m4 - 1];
-      xv[h][t] = j < a.m4 ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+      if constexpr (MASK) xv[h][t] = v;
+      else xv[h][t] = j < a.m4 ? v : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
+  if constexpr (MASK && NP * T4 > 16) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int h = 0; h < NP; ++h) {
     float acc = 0.f;
-    if (a.ip) {
+    if constexpr (MASK) {
+#pragma unroll
+      for (int t = 0; t < T4; ++t) {
+        const int j = lg + G * t;
+        const uint32_t in = j < a.m4 ? ~0u : 0u;
+        const float4 q = qlds != nullptr ? qlds[j < a.m4 ? j : a.m4 - 1] : qv[t];
+        const float u = a.ip ? -piece_prod(q, xv[h][t]) : piece_sq<false>(q, xv[h][t]);
+        const float w = __uint_as_float(__float_as_uint(u) & in);
+        acc = t == 0 ? w : acc + w;
+      }
+    } else if (a.ip) {
       // inner-product metric: the distance is -q.x
 #pragma unroll
       for (int t = 0; t < T4; ++t) {
@@ -551,7 +563,7 @@ __device__ __forceinline__ void dists_pass(const KArgs& a, const float4* qv, con
   }
 }
 
-template <int G, int T4, int NP, int WNP, bool EXACT>
+template <int G, int T4, int NP, int WNP, bool EXACT, bool MASK>
 __device__ __forceinline__ float dists_passes(const KArgs& a, const float4* qv, const float4* qlds,
                                               const int* __restrict__ ids_lds, int cnt) {
   constexpr int NPP = 64 / G;
@@ -559,15 +571,15 @@ __device__ __forceinline__ float dists_passes(const KArgs& a, const float4* qv, 
   int p0 = 0;
   if constexpr (WNP > NP) {
     for (; cnt - p0 > WNP / 2 * NPP; p0 += WNP * NPP)
-      dists_pass<G, T4, WNP, EXACT>(a, qv, qlds, ids_lds, cnt, p0, mine);
+      dists_pass<G, T4, WNP, EXACT, MASK>(a, qv, qlds, ids_lds, cnt, p0, mine);
     if constexpr (WNP / 2 > NP) {
       if (cnt - p0 > WNP / 4 * NPP) {
-        dists_pass<G, T4, WNP / 2, EXACT>(a, qv, qlds, ids_lds, cnt, p0, mine);
+        dists_pass<G, T4, WNP / 2, EXACT, MASK>(a, qv, qlds, ids_lds, cnt, p0, mine);
         p0 += WNP / 2 * NPP;
       }
     }
   }
-  for (; p0 < cnt; p0 += NP * NPP) dists_pass<G, T4, NP, EXACT>(a, qv, qlds, ids_lds, cnt, p0, mine);
+  for (; p0 < cnt; p0 += NP * NPP) dists_pass<G, T4, NP, EXACT, MASK>(a, qv, qlds, ids_lds, cnt, p0, mine);
   return mine;
 }
 
@@ -576,11 +588,11 @@ __device__ __forceinline__ float dists_passes(const KArgs& a, const float4* qv, 
 // of 64 / G vectors; with WNP > NP first as many wide passes (WNP groups) as
 // the count fills more than half, then one half as wide if that is filled
 // more than half.
-template <int G, int T4, int NP, int WNP>
+template <int G, int T4, int NP, int WNP, bool MASK>
 __device__ __forceinline__ float exact_dists(const KArgs& a, const float4* qv, const float4* qlds,
                                              const int* __restrict__ ids_lds, int cnt) {
-  if (a.m4 == G * T4 && !a.ip) return dists_passes<G, T4, NP, WNP, true>(a, qv, qlds, ids_lds, cnt);
-  return dists_passes<G, T4, NP, WNP, false>(a, qv, qlds, ids_lds, cnt);
+  if (a.m4 == G * T4 && !a.ip) return dists_passes<G, T4, NP, WNP, true, false>(a, qv, qlds, ids_lds, cnt);
+  return dists_passes<G, T4, NP, WNP, false, MASK>(a, qv, qlds, ids_lds, cnt);
 }
 
 // Groups of 64 / G vectors whose loads are in flight together in a pass:
@@ -599,6 +611,20 @@ constexpr int vectors_in_flight_wide() {
   if (G == 8 || (MODE != FINGER_MODE_PLAIN && MODE != FINGER_MODE_FINGER)) return 0;
   if (!WIDE) return MODE == FINGER_MODE_FINGER && G == 32 && T4 == 4 ? 2 : 0;
   return T4 == 8 ? 4 : 8;
+}
+
+// Whether the distances of vectors whose pieces the lanes do not cover exactly
+// mask the terms past the vector, with all loads of a pass in flight together,
+// or zero the pieces, which compiles to a branch and a wait at each load.  The
+// masked form holds 10 to 16 more registers a lane.  Masked where it takes no
+// resident wave or pays for it: collection of training pairs (960 dims, 1,000
+// queries: 1,065 us with branches, 770 masked) and the per-lane screen of
+// packed codes (1,028 dims, bf16, 20,000 queries, ef 100: 0.81 times).  Not in
+// the other instances: 3,500 queries x 960 plain take up to 1.25 times as long
+// with the waves it costs them, 20,000 x 1,028 with f32 codes 1.07 times.
+template <int MODE, int CODE, int LC>
+constexpr bool masked_terms() {
+  return MODE == kModeLog || (MODE == FINGER_MODE_FINGER && LC == 0 && CODE != FINGER_CODE_F32);
 }
 
 typedef __bf16 b8v __attribute__((ext_vector_type(8)));
@@ -863,7 +889,8 @@ __device__ __forceinline__ void search_body(const KArgs& a) {
       visit_rest(entry, got, spilled, overflow);
     }
     wave_lds_sync();
-    const float d_entry = exact_dists<G, T4, 1, 0>(a, qv, qlds, cid, 1);
+    constexpr bool kMask = MODE != kModeLog && masked_terms<MODE, CODE, LC>();  // (collecting: same speed, more registers)
+    const float d_entry = exact_dists<G, T4, 1, 0, kMask>(a, qv, qlds, cid, 1);
     // T lives in registers when it fits one entry per lane (ef_max <= 64):
     // lane i holds entry i as td (distance) and ti (id with the expanded
     // bit); selection and merge then read no memory.  Larger lists live in
@@ -1229,7 +1256,8 @@ __device__ __forceinline__ void search_body(const KArgs& a) {
       if (S2 == 0) continue;
       // 5. exact distances of the survivors
       const float dmine = exact_dists<G, T4, vectors_in_flight<MODE, G, T4>(),
-                                      vectors_in_flight_wide<MODE, G, T4, WIDE>()>(a, qv, qlds, cid, S2);
+                                      vectors_in_flight_wide<MODE, G, T4, WIDE>(),
+                                      masked_terms<MODE, CODE, LC>()>(a, qv, qlds, cid, S2);
 
       // 6. admission: lanes 0..S2-1 hold (dmine, cid)
       uint64_t key = ~0ull;
