@@ -551,7 +551,9 @@ __global__ void __launch_bounds__(256) k_knn_select(SelectArgs a) {
     }
     return;
   }
-  if (N <= a.KK) {
+  // Too few points so far: any further one is kept.  (Not with KK: a phase that
+  // appends nothing leaves the bound, or the next one would append everything.)
+  if (N < a.KK) {
     for (int i = l; i < a.KK; i += 64) best[i] = i < N ? (((uint64_t)D[i] << 32) | I[i]) : ~0ull;
     if (l == 0) {
       a.tauk[row] = ~0ull;
