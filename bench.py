@@ -59,7 +59,7 @@ def kernel_source_hash() -> str:
     lines are dropped, so that editing a comment keeps counters taken on the
     same code valid."""
     h = hashlib.sha256()
-    for f in ("search_kernel.h", "search.hip", "device_common.h"):
+    for f in ("search_kernel.h", "search_rule.h", "search.hip", "device_common.h"):
         with open(os.path.join(ROOT, "paper_2206_11408_amd", "csrc", f)) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
