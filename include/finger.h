@@ -396,8 +396,11 @@ typedef struct finger_graph_stats {
  *             padded; repair edges follow the row's own entries.
  *   stats     host, or NULL.
  * The kNN runs in query batches of at most 2^20 points.  Synchronous;
- * allocates its scratch (about 2nk * 40 bytes plus one batch's kNN candidate
- * lists) and frees it before returning.
+ * allocates its scratch and frees it before returning: about 2nk * 40 bytes,
+ * after the kNN's workspace (finger_exact_knn_workspace_size for n points and
+ * one batch; 1.9 GB for 1M x 960) is freed.  Where the device cannot give that
+ * workspace, one of about a sixteenth is tried before ENOMEM (slower, the same
+ * graph).  The repair takes the workspace of a batch of starting nodes again.
  * Errors: EINVAL (NULL pointers, n < 2, m, knn_k outside 1..min(n - 1, 127),
  * max_degree outside 1..64, metric not L2/ANGULAR, entry out of range),
  * EOVERFLOW (2 n knn_k >= 2^31, or no reached node has a free slot for a
@@ -500,7 +503,10 @@ FINGER_API int finger_estimate_edges(const finger_tables* t, const float* querie
 
 /* ----------------------------------------------------------- exact kNN */
 
-/* Workspace for finger_exact_knn. */
+/* Workspace for finger_exact_knn: at most 1 GB for the points in split
+ * precision (a window of them at a time) and about 1 GB for the candidates of
+ * 65,536 queries (2 GB with k = 128), with 4 bytes a point (12 a point and 8 a
+ * query for the angular metric, which the size allows for). */
 FINGER_API int finger_exact_knn_workspace_size(int64_t n, int32_t m, int64_t nq, int32_t k,
                                     size_t* bytes /* host */);
 
