@@ -837,7 +837,8 @@ int knn_region(int cap, int nch) { return nch == 1 ? cap : (cap + nch - 1) / nch
 // 12 bytes moved per element against 2 x 65,536 operations), and the keys those
 // of kRowBatch rows.  Both are 1/16 of that where the caller asks for a small
 // workspace.  Neither changes a result: the KK smallest keys do not depend on
-// where a phase ends.
+// where a phase ends.  Several windows cost calls of few queries up to 8% (one
+// query x 400,000 x 2,048: 3.0 ms, 2.8 with all points held; 5,000 the same).
 constexpr size_t kKnnPlanes = (size_t)1 << 30;
 
 KnnPlan knn_plan(int64_t n, int m, int64_t nq, int k, const KnnSpace& space) {
