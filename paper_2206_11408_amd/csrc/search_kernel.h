@@ -618,13 +618,14 @@ constexpr int vectors_in_flight_wide() {
 // or zero the pieces, which compiles to a branch and a wait at each load.  The
 // masked form holds 10 to 16 more registers a lane.  Masked where it takes no
 // resident wave or pays for it: collection of training pairs (960 dims, 1,000
-// queries: 1,065 us with branches, 770 masked) and the per-lane screen of
-// packed codes (1,028 dims, bf16, 20,000 queries, ef 100: 0.81 times).  Not in
+// queries: 1,065 us with branches, 770 masked) and the per-lane screen beyond
+// 128 dimensions (20,000 queries, ef 100, masked against branches: 300 dims,
+// bf16 and rank 96 1.19 times as fast; 480 f32 1.05; 1,028 f32 1.7).  Not in
 // the other instances: 3,500 queries x 960 plain take up to 1.25 times as long
 // with the waves it costs them, 20,000 x 1,028 with f32 codes 1.07 times.
-template <int MODE, int CODE, int LC>
+template <int MODE, int G, int LC>
 constexpr bool masked_terms() {
-  return MODE == kModeLog || (MODE == FINGER_MODE_FINGER && LC == 0 && CODE != FINGER_CODE_F32);
+  return MODE == kModeLog || (MODE == FINGER_MODE_FINGER && LC == 0 && G > 8);
 }
 
 typedef __bf16 b8v __attribute__((ext_vector_type(8)));
@@ -889,7 +890,7 @@ __device__ __forceinline__ void search_body(const KArgs& a) {
       visit_rest(entry, got, spilled, overflow);
     }
     wave_lds_sync();
-    constexpr bool kMask = MODE != kModeLog && masked_terms<MODE, CODE, LC>();  // (collecting: same speed, more registers)
+    constexpr bool kMask = MODE != kModeLog && masked_terms<MODE, G, LC>();  // (collecting: same speed, more registers)
     const float d_entry = exact_dists<G, T4, 1, 0, kMask>(a, qv, qlds, cid, 1);
     // T lives in registers when it fits one entry per lane (ef_max <= 64):
     // lane i holds entry i as td (distance) and ti (id with the expanded
@@ -1257,7 +1258,7 @@ __device__ __forceinline__ void search_body(const KArgs& a) {
       // 5. exact distances of the survivors
       const float dmine = exact_dists<G, T4, vectors_in_flight<MODE, G, T4>(),
                                       vectors_in_flight_wide<MODE, G, T4, WIDE>(),
-                                      masked_terms<MODE, CODE, LC>()>(a, qv, qlds, cid, S2);
+                                      masked_terms<MODE, G, LC>()>(a, qv, qlds, cid, S2);
 
       // 6. admission: lanes 0..S2-1 hold (dmine, cid)
       uint64_t key = ~0ull;
@@ -1446,23 +1447,30 @@ hipError_t launch_fn(F fn, const KArgs& a, int blocks, int lds, hipStream_t s) {
 template <int MODE, int CODE, int G, int T4, bool PF, int LC>
 hipError_t launch_k(const KArgs& a, int blocks, int lds, hipStream_t s) {
   constexpr bool kPlain = MODE == FINGER_MODE_PLAIN, kFinger = MODE == FINGER_MODE_FINGER;
-  // shapes with a wide instance: in FINGER mode of 260 to 512 dimensions only
-  // the coalesced screen's that requests codes after the visited test
+  // shapes with a wide instance: in FINGER mode of 132 to 512 dimensions only
+  // the coalesced screen's (of 260 to 512 only where codes are requested after
+  // the visited test).  The per-lane screen of f32 codes beyond 1,024
+  // dimensions has no other, as its narrow passes leave two waves a SIMD too.
   constexpr bool kFew = (kPlain && G == 32) || (kFinger && G == 32 && T4 == 4 && LC > 0 && !PF);
-  constexpr bool kWide = kFew || ((kPlain || kFinger) && (G == 64 || (G == 32 && T4 == 2)));
-  if constexpr (kWide)
-    if (wide_passes(kPlain, G, T4, a.nq, blocks * a.waves_per_block, a.cus)) {
-      if constexpr (kFew) return launch_fn(k_search_few<MODE, CODE, G, T4, LC>, a, blocks, lds, s);
-      else return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, true>, a, blocks, lds, s);
-    }
-  // the register cap is for narrow passes of up to 512 dimensions: wide ones
-  // would spill (256 dimensions, bf16, 1,024 queries: 158 us capped, 149
-  // not), and at 8 float4 per lane a capped build also returned run-to-run
-  // differing results with BF16 codes requested ahead
-  if constexpr (kFinger && G < 64)
-    return launch_fn(k_search_w4<MODE, CODE, G, T4, PF, LC>, a, blocks, lds, s);
-  else
-    return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, false>, a, blocks, lds, s);
+  constexpr bool kWide = kFew || (kPlain && G > 8) || (kFinger && (G == 64 || (G == 32 && T4 == 2 && LC > 0)));
+  constexpr bool kOnlyWide = kFinger && T4 == 8 && LC == 0 && CODE == FINGER_CODE_F32;
+  if constexpr (kOnlyWide) {
+    return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, true>, a, blocks, lds, s);
+  } else {
+    if constexpr (kWide)
+      if (wide_passes(kPlain, G, T4, a.nq, blocks * a.waves_per_block, a.cus)) {
+        if constexpr (kFew) return launch_fn(k_search_few<MODE, CODE, G, T4, LC>, a, blocks, lds, s);
+        else return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, true>, a, blocks, lds, s);
+      }
+    // the register cap is for narrow passes of up to 512 dimensions: wide ones
+    // would spill (256 dimensions, bf16, 1,024 queries: 158 us capped, 149
+    // not), and at 8 float4 per lane a capped build also returned run-to-run
+    // differing results with BF16 codes requested ahead
+    if constexpr (kFinger && G < 64)
+      return launch_fn(k_search_w4<MODE, CODE, G, T4, PF, LC>, a, blocks, lds, s);
+    else
+      return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, false>, a, blocks, lds, s);
+  }
 }
 
 // Lanes per vector and float4 per lane: as few float4 as cover m (a lane's
@@ -1471,6 +1479,8 @@ hipError_t launch_k(const KArgs& a, int blocks, int lds, hipStream_t s) {
 // count does not change the sum.  Measured (10,000 queries, 120,000 x 960,
 // fp8 codes, narrow passes): 4 pieces a lane 1.76 ms against 2.03 ms with 8;
 // 20,000 queries x 96 dimensions, 3 pieces 5.53 ms against 5.65 ms with 4.
+// The per-lane screen has fewer shapes (two pieces with f32 codes: 200 dims,
+// rank 128 1.15 times as fast as with four).
 template <int MODE, int CODE, bool PF, int LC>
 hipError_t launch_dims_lc(const KArgs& a, int blocks, int lds, hipStream_t s) {
   if constexpr (MODE == FINGER_MODE_PLAIN || (MODE == FINGER_MODE_FINGER && LC > 0)) {
@@ -1479,7 +1489,7 @@ hipError_t launch_dims_lc(const KArgs& a, int blocks, int lds, hipStream_t s) {
     if (a.m4 <= 24) return launch_k<MODE, CODE, 8, 3, PF, LC>(a, blocks, lds, s);
   }
   if (a.m4 <= 32) return launch_k<MODE, CODE, 8, 4, PF, LC>(a, blocks, lds, s);
-  if constexpr (MODE == FINGER_MODE_PLAIN || (MODE == FINGER_MODE_FINGER && LC > 0))
+  if constexpr (MODE == FINGER_MODE_PLAIN || (MODE == FINGER_MODE_FINGER && (LC > 0 || CODE == FINGER_CODE_F32)))
     if (a.m4 <= 64) return launch_k<MODE, CODE, 32, 2, PF, LC>(a, blocks, lds, s);
   if (a.m4 <= 128) return launch_k<MODE, CODE, 32, 4, PF, LC>(a, blocks, lds, s);
   if constexpr (MODE == FINGER_MODE_PLAIN || MODE == FINGER_MODE_FINGER)

@@ -46,7 +46,8 @@ def test_wide_pass_loads_together(tmp_path, kernel, loads):
 
 @NEEDS_HIPCC
 @pytest.mark.parametrize("kernel,loads", [("k_search<3, FINGER_CODE_BF16, 64, 8, false, 0, false>", 8),
-                                          ("k_search<FINGER_MODE_FINGER, FINGER_CODE_BF16, 64, 8, false, 0, true>", 32)])
+                                          ("k_search<FINGER_MODE_FINGER, FINGER_CODE_BF16, 64, 8, false, 0, true>", 32),
+                                          ("k_search<FINGER_MODE_FINGER, FINGER_CODE_F32, 64, 8, false, 0, true>", 32)])
 def test_masked_pass_loads_together(tmp_path, kernel, loads):
     # (once for vectors that the lanes cover exactly, once for any other)
     assert sum(r >= loads for r in runs_of_loads(tmp_path, kernel)) >= 2
