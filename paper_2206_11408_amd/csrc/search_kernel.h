@@ -1458,7 +1458,7 @@ hipError_t launch_k(const KArgs& a, int blocks, int lds, hipStream_t s) {
     return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, true>, a, blocks, lds, s);
   } else {
     if constexpr (kWide)
-      if (wide_passes(kPlain, G, T4, a.nq, blocks * a.waves_per_block, a.cus)) {
+      if (wide_passes(kPlain, G, T4, a.nq, blocks * a.waves_per_block, a.cus, a.persistent != 0 && a.efq != nullptr)) {
         if constexpr (kFew) return launch_fn(k_search_few<MODE, CODE, G, T4, LC>, a, blocks, lds, s);
         else return launch_fn(k_search<MODE, CODE, G, T4, PF, LC, true>, a, blocks, lds, s);
       }

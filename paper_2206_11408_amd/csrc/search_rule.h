@@ -27,10 +27,18 @@ constexpr int wide_waves_per_cu(bool plain, int g, int t4) {
 // of 132 to 256 dimensions in FINGER mode and of 516 to 1,024 win again
 // (10,000 queries: 256 bf16 1.23 / 1.02, 960 fp8 1.17 / 0.98, 960 plain 0.97 /
 // 1.07); the other shapes' do not.
-constexpr bool wide_passes(bool plain, int g, int t4, int64_t nq, int64_t waves, int cus) {
+//
+// `mixed`: queries of different ef from a queue.  There is no round of waves to
+// fill, and of the shapes that win again with many queries 132 to 256
+// dimensions win at every size (256 dimensions, ef 12 to 101, 3,500 to 7,000
+// queries: 1.08 to 1.15; 132: 1.02 to 1.05), 516 to 1,024 up to 12 queries a CU
+// (2,500 and 3,000 queries: 516 1.02 to 1.11, 768 1.02 to 1.15, 1,024 1.06 to
+// 1.30; beyond, 516 dimensions lose down to 0.77).
+constexpr bool wide_passes(bool plain, int g, int t4, int64_t nq, int64_t waves, int cus, bool mixed = false) {
   if (g == 8) return false;
   if (nq <= (int64_t)wide_waves_per_cu(plain, g, t4) * cus || waves <= (int64_t)8 * cus) return true;
-  return (g == 64 ? t4 == 4 : t4 == 2 && !plain) && nq >= (int64_t)36 * cus;
+  const bool again = g == 64 ? t4 == 4 : t4 == 2 && !plain;
+  return again && (mixed ? g == 32 || nq <= (int64_t)12 * cus : nq >= (int64_t)36 * cus);
 }
 
 // Workgroups of a static launch (query i belongs to workgroup i mod blocks).

@@ -1,6 +1,7 @@
 """The launch rules of the search (host arithmetic, compiled by itself)."""
 import os
 import subprocess
+import tempfile
 
 import pytest
 
@@ -72,3 +73,19 @@ def test_static_grid_is_what_is_resident(ask):
     # a workgroup per query, or all of them resident
     assert ask([("r", 4096, 4096, 8, CUS), ("r", 1000, 1000, 2, CUS), ("r", 3072, 20_000, 16, CUS),
                 ("r", 3072, 20_000, 0, CUS)]) == [4096, 1000, 3072, 3072]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_queue_of_mixed_ef(ask, shape):
+    src = PROGRAM.replace("(a, b, c, d, e, f)", "(a, b, c, d, e, f, true)")
+    assert src != PROGRAM
+    many = shape in ((0, 32, 2), (0, 64, 4), (1, 64, 4))
+    with tempfile.TemporaryDirectory() as d:
+        with open(os.path.join(d, "rule.cpp"), "w") as fh:
+            fh.write(src)
+        subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2206_11408_amd", "csrc"),
+                        os.path.join(d, "rule.cpp"), "-o", os.path.join(d, "rule")], check=True)
+        text = "".join(f"w {shape[0]} {shape[1]} {shape[2]} {nq} {min(nq, 4096)} {CUS}\n" for nq in (33, 12 * CUS, 12 * CUS + 1, 8000, 100_000))
+        out = subprocess.run([os.path.join(d, "rule")], input=text, capture_output=True, text=True, check=True).stdout
+    always, resident = shape == (0, 32, 2), shape == (1, 32, 2)
+    assert [int(v) for v in out.split()] == [1, many or resident, always or resident, always, always]
